@@ -76,11 +76,12 @@ typedef enum {
 
 typedef enum {
   MD_LJ_AUTO = 0,       /* chosen by the autotuner at init */
-  MD_LJ_ATOM = 1,       /* one lane per home atom walking the neighbouring cells */
-  MD_LJ_CELLTILE = 2,   /* one wavefront per home cell: home atoms wave-uniform, candidate
-                           atoms across the lanes */
+  MD_LJ_ATOM = 1,       /* per atom order: groups of home atoms that follow one another along x,
+                           a wavefront per group, each lane the pair of one home and one candidate */
+  MD_LJ_CELLTILE = 2,   /* mixed precision: one wavefront per home cell, home atoms wave-uniform,
+                           candidate atoms across the lanes; FP64: as MD_LJ_ATOM */
   MD_LJ_CELLTILE_NB = 3, /* as MD_LJ_CELLTILE, with the pair force evaluated on every lane and
-                            zeroed outside the cutoff instead of branching (mixed precision) */
+                            zeroed outside the cutoff instead of branching (mixed precision; FP64: as MD_LJ_ATOM) */
   MD_LJ_NLIST = 4,       /* neighbour-list mode (nl_skin > 0): a Verlet list per atom, one lane
                             per atom walking it */
   MD_LJ_NLIST_TILE = 5,  /* neighbour-list mode: a list per cell (every atom within rc + skin of

@@ -196,10 +196,40 @@ struct Plan {
   std::vector<int32_t> chunk_rng;           // [2 * chunks] first and end partial
   int64_t nl_entries = 0;
   bool half = false;                        // half-shell LJ: fixed-point force accumulators
+  bool group = false;                       // cell path through the group kernel (group_kernel)
   int prec = 0;
   int chain_len = 1;
   std::vector<BoxDev> boxes;
 };
+
+// The group kernel (md_group.hip) runs MD_LJ_ATOM in both precisions and the FP64 form of the two cell
+// tiles: at 300,000 atoms, R = 2, it took 205 us against 242 us for the FP64 cell tile it replaces,
+// but 172 us against 139 us for the mixed one.
+bool group_kernel(const md_config* cfg, int kernel) {
+  if (cfg->nl_skin > 0.0) return false;
+  return kernel == MD_LJ_ATOM || (cfg->precision == MD_PREC_FP64 && (kernel == MD_LJ_CELLTILE || kernel == MD_LJ_CELLTILE_NB));
+}
+
+// Work of the group kernel in a box of n atoms: lj_slots waves per row of cells, each taking every
+// lj_slots-th group of the row (a row of a melt holds its mean +- a few per cent; fuller rows give
+// some waves a second group), on at most one block per 4 atoms (their energy partials live in the
+// bins' scratch, see carve) plus the padding.
+void group_work(const md_forcefield* ff, const md_config* cfg, int64_t n, BoxDev* B) {
+  const int64_t rows = (int64_t)B->M[1] * B->M[2];
+  const double per_row = (double)n / (double)rows;
+  B->lj_slots = (int32_t)std::ceil(1.04 * per_row / kGroupHomes + 0.25);
+  B->lj_items = (int32_t)(rows * B->lj_slots);
+  const int64_t most = std::max<int64_t>(n / 4, 1);
+  B->lj_blocks = (int32_t)((std::min<int64_t>(B->lj_items, most) + kGroupPad - 1) / kGroupPad * kGroupPad);
+  B->lj_waves = B->lj_items <= kSplitItems ? kSplit : 1;
+  B->inv_slots = 1.0 / (double)B->lj_slots;
+  B->inv_m1 = 1.0 / (double)B->M[1];
+  for (int d = 0; d < 3; ++d) B->L_q[d] = fix_coord(B->L[d]);
+  // a group's candidates lie within lj_cap + rc + edge of its first atom; in the mixed form that
+  // must stay below 64 A (payload_ok: (R + 2) edge < 63 A, so the cap is at least edge - 1)
+  B->lj_cap = ff->rc;
+  if (cfg->precision == MD_PREC_MIXED) B->lj_cap = std::min(ff->rc, 62.0 - ff->rc - B->edge[0]);
+}
 
 // List capacity (a list that fills up is reported as MD_ERR_NLIST).  Per-atom lists: the
 // pairs within rc + skin at the densest box's density, 1.5x plus 64.  Per-cell lists: the
@@ -233,6 +263,7 @@ Plan make_plan(const md_forcefield* ff, const md_config* cfg, int R, int kernel)
   p.chain_len = cfg->chain_len;
   const bool nl = cfg->nl_skin > 0.0;
   p.half = !nl && kernel == MD_LJ_HALFSHELL;
+  p.group = group_kernel(cfg, kernel);
   if (nl) {
     if (kernel != MD_LJ_NLIST_TILE) kernel = MD_LJ_NLIST;
     p.nl_cap = nl_capacity(ff, cfg, R, kernel);
@@ -268,6 +299,11 @@ Plan make_plan(const md_forcefield* ff, const md_config* cfg, int R, int kernel)
     atom += n;
     cell += nc;
     blk += (n + kAtomBlock - 1) / kAtomBlock;
+    if (p.group) {
+      group_work(ff, cfg, n, &p.boxes.emplace_back(B));
+      lblk += p.boxes.back().lj_blocks;
+      continue;
+    }
     lblk += lj_blocks_for_box(kernel, n, nc);
     if (nl) {
       cblk += (nc + kTileWaves - 1) / kTileWaves;
@@ -318,14 +354,32 @@ size_t carve(const Plan& p, char* base, Views* v) {
   t.n_boxes = p.n_boxes;
   t.n_atom_blocks = p.n_atom_blocks;
   t.n_lj_blocks = p.n_lj_blocks;
+  for (const BoxDev& B : p.boxes) t.lj_wave_mask |= B.lj_waves == kSplit ? 2 : 1;
   t.boxes = (const BoxDev*)take(sizeof(BoxDev) * p.n_boxes);
   t.blk_box = (const int32_t*)take(4 * (size_t)p.n_atom_blocks);
-  t.lj_blk_box = (const int32_t*)take(4 * (size_t)p.n_lj_blocks);
-  t.cell = (int32_t*)take(4 * (size_t)p.N);
-  t.slot = (int32_t*)take(4 * (size_t)p.N);
+  t.lj_blk_box = (const int32_t*)take(4 * (size_t)(p.group ? p.n_lj_blocks / kGroupPad : p.n_lj_blocks));
+  if (p.group) {
+    // one scratch area for what never lives at the same time: the bins' working arrays (from the
+    // count to the rank), the LJ energy partials (from the force kernel to the reduction) and the
+    // observables' block partials
+    const size_t N = (size_t)p.N, part = sizeof(dd) * 3 * (size_t)p.n_lj_blocks;
+    char* q = take(std::max({16 * N, part, 4 * (size_t)kObsBlocks * kMaxObsBins}));
+    t.cell = (int32_t*)q;
+    t.slot = q ? t.cell + N : nullptr;
+    t.tmp = q ? t.slot + N : nullptr;
+    t.key = q ? (uint32_t*)(t.tmp + N) : nullptr;
+    t.part_lj = (dd*)q;
+    t.obs_part = (uint32_t*)q;
+  } else {
+    t.cell = (int32_t*)take(4 * (size_t)p.N);
+    t.slot = (int32_t*)take(4 * (size_t)p.N);
+    t.tmp = (int32_t*)take(4 * (size_t)p.N);
+    t.part_lj = (dd*)take(sizeof(dd) * 3 * (size_t)p.n_lj_blocks);
+    t.obs_part = (uint32_t*)take(4 * (size_t)kObsBlocks * kMaxObsBins);
+    t.shift_tab = take((p.prec == MD_PREC_MIXED ? 12 : 24) * (size_t)kShiftSlots * p.n_boxes);
+  }
   t.cnt = (int32_t*)take(4 * (size_t)p.C);
   t.cell_start = (int32_t*)take(4 * (size_t)(p.C + 1));
-  t.tmp = (int32_t*)take(4 * (size_t)p.N);
   t.cell_atoms = (int32_t*)take(4 * (size_t)p.N);
   t.scell = (int32_t*)take(4 * (size_t)p.N);
   t.payload = take(psz * (size_t)p.N);
@@ -333,13 +387,10 @@ size_t carve(const Plan& p, char* base, Views* v) {
   t.f_tot = take(3 * fsz * (size_t)p.N);
   if (p.half) t.f_acc = (unsigned long long*)take(24 * (size_t)p.N);
   t.scan_tiles = (int32_t*)take(4 * (size_t)p.n_tiles);
-  t.part_lj = (dd*)take(sizeof(dd) * 3 * (size_t)p.n_lj_blocks);
   t.part_bd = (dd*)take(sizeof(dd) * kBdParts * (size_t)p.n_atom_blocks);
   t.thermo = (double*)take(8 * kThermo * (size_t)p.n_boxes);
   t.energy = (double*)take(8 * kEnergySlots * (size_t)p.n_boxes);
   t.err = (int32_t*)take(4);
-  t.obs_part = (uint32_t*)take(4 * (size_t)kObsBlocks * kMaxObsBins);
-  t.shift_tab = take((p.prec == MD_PREC_MIXED ? 12 : 24) * (size_t)kShiftSlots * p.n_boxes);
   t.n_bd_chunks = p.n_bd_chunks;
   t.n_lj_chunks = p.n_lj_chunks;
   t.l1_bd = p.l1_bd;
@@ -437,12 +488,15 @@ md_status configure(md_ctx* c, const md_config* cfg, int R, int kernel) {
   v.pos = c->pos;
   v.vel = c->vel;
   v.type = c->type;
-  std::vector<int32_t> bb(p.n_atom_blocks), lb(p.n_lj_blocks), cb(p.n_cell_blocks);
+  std::vector<int32_t> bb(p.n_atom_blocks), lb(p.group ? p.n_lj_blocks / kGroupPad : p.n_lj_blocks), cb(p.n_cell_blocks);
   for (int b = 0; b < p.n_boxes; ++b) {
     const int32_t e1 = b + 1 < p.n_boxes ? p.boxes[b + 1].blk_off : p.n_atom_blocks;
     for (int32_t k = p.boxes[b].blk_off; k < e1; ++k) bb[k] = b;
     const int32_t e2 = b + 1 < p.n_boxes ? p.boxes[b + 1].lj_blk_off : p.n_lj_blocks;
-    for (int32_t k = p.boxes[b].lj_blk_off; k < e2; ++k) lb[k] = b;
+    if (p.group)
+      for (int32_t k = p.boxes[b].lj_blk_off; k < e2; k += kGroupPad) lb[k / kGroupPad] = b;
+    else
+      for (int32_t k = p.boxes[b].lj_blk_off; k < e2; ++k) lb[k] = b;
     const int32_t e3 = b + 1 < p.n_boxes ? p.boxes[b + 1].cell_blk_off : p.n_cell_blocks;
     for (int32_t k = p.boxes[b].cell_blk_off; k < e3; ++k) cb[k] = b;
   }
@@ -470,7 +524,7 @@ md_status configure(md_ctx* c, const md_config* cfg, int R, int kernel) {
   if ((st = hip_check(c, hipMemcpy((void*)v.chunk_rng, p.chunk_rng.data(), 4 * p.chunk_rng.size(),
                                    hipMemcpyHostToDevice), "upload reduction chunks")))
     return st;
-  if (R <= kTileMaxR) {
+  if (v.shift_tab && R <= kTileMaxR) {
     // stencil shifts per box in the payload's units, and the sentinel slot
     const int W = 2 * R + 1;
     std::vector<int32_t> qi((size_t)3 * kShiftSlots * p.n_boxes, 0);
@@ -541,6 +595,8 @@ void enqueue_forces(md_ctx* c, hipStream_t s, bool kick, bool energy) {
   const bool fp32 = c->prec == MD_PREC_MIXED;
   if (nl_mode(c))
     launch_lj_nl(c->v, c->ffd, fp32, c->lj_kernel, energy, c->homes, s);
+  else if (c->v.key)
+    launch_lj_group(c->v, c->ffd, fp32, energy, s);
   else
     launch_lj(c->v, c->ffd, fp32, c->lj_kernel, energy, c->homes, s);
   launch_bonded(c->v, c->ffd, fp32, bonded_mode(c, kick), energy, kick && c->remove_com, c->dt, s);
@@ -624,7 +680,8 @@ md_status autotune(md_ctx* c, const md_config* cfg, int* bestR, int* bestK, int*
     Rs.erase(std::remove_if(Rs.begin(), Rs.end(), [](int R) { return R > kTileMaxR; }), Rs.end());
   } else if (cfg->lj_kernel) Ks.push_back(cfg->lj_kernel);
   else {
-    Ks.push_back(MD_LJ_ATOM);
+    // (FP64: every kernel 1..3 is the group kernel)
+    if (cfg->precision == MD_PREC_MIXED) Ks.push_back(MD_LJ_ATOM);
     Ks.push_back(MD_LJ_CELLTILE);
     if (cfg->precision == MD_PREC_MIXED) Ks.push_back(MD_LJ_CELLTILE_NB);
   }
@@ -926,6 +983,8 @@ md_status md_step_timed(md_ctx* c, int32_t n_steps, double* ms_out) {
     (void)hipEventRecord(e[8], s);
     if (nl)
       launch_lj_nl(c->v, c->ffd, fp32, c->lj_kernel, last, c->homes, s);
+    else if (c->v.key)
+      launch_lj_group(c->v, c->ffd, fp32, last, s);
     else
       launch_lj(c->v, c->ffd, fp32, c->lj_kernel, last, c->homes, s);
     (void)hipEventRecord(e[9], s);

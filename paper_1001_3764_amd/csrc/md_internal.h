@@ -10,7 +10,6 @@
 namespace mdk {
 
 constexpr int kAtomBlock = 256;   // threads per block of every per-atom kernel
-constexpr int kLjAtomBlock = 128; // threads per block of the lane-per-atom LJ kernel
 constexpr int kScanItems = 4;     // cells per thread in the scan
 constexpr int kScanBlock = 1024;
 constexpr int kScanTile = kScanItems * kScanBlock;
@@ -28,6 +27,19 @@ constexpr int kFixBits = 25;
 constexpr double kFix = 33554432.0;               // 2^25
 constexpr float kInvFixF = 2.98023223876953125e-8f;   // 2^-25
 constexpr float kInvFix2F = 8.8817841970012523e-16f;  // 2^-50
+
+// x >= 0 in fixed-point units modulo 2^32, rounded to nearest: the low word of 2^27 + x, whose ulp
+// is 2^-25 (x below 2^27 A)
+__host__ __device__ inline int32_t fix_coord(double x) {
+  const double y = 134217728.0 + x;
+#ifdef __HIP_DEVICE_COMPILE__
+  return __double2loint(y);
+#else
+  uint64_t b;
+  __builtin_memcpy(&b, &y, 8);
+  return (int32_t)(uint32_t)b;
+#endif
+}
 
 // tag of a sorted atom: global index << 4 | type << 3 | (cell x-index & 7)
 __host__ __device__ inline int32_t tag_index(int32_t tag) { return tag >> 4; }
@@ -51,6 +63,12 @@ struct BoxDev {
   double dof;             // 3N - 3
   double inv_mass;        // 1 / total mass of the box
   int64_t nl_off;         // first entry of this box's neighbour lists
+  // group kernel (md_group.hip): work items (lj_slots per row of cells) and blocks of this box
+  int32_t lj_slots, lj_items, lj_blocks;
+  int32_t lj_waves;       // wavefronts per group: 1, or kSplit in small boxes
+  int32_t L_q[3];         // edges in fixed-point units, modulo 2^32
+  double inv_slots, inv_m1;   // 1 / lj_slots, 1 / M[1]
+  double lj_cap;          // A: extent along x of a group of home atoms
   // first-level chunks of the per-box reduction (kReduceChunk block partials each)
   int32_t bd_chunk_off, bd_chunks;   // of the bonded/kinetic partials
   int32_t lj_chunk_off, lj_chunks;   // of the LJ partials (numbered after all bonded chunks)
@@ -123,9 +141,10 @@ struct Views {
   int64_t N, C;            // atoms, cells (all boxes)
   int32_t n_boxes, R;
   int32_t n_atom_blocks, n_lj_blocks;
+  int32_t lj_wave_mask;    // group kernel: bit 0 / 1: some box has one / kSplit waves per group
   const BoxDev* boxes;
   const int32_t* blk_box;      // [n_atom_blocks] box of each per-atom block
-  const int32_t* lj_blk_box;   // [n_lj_blocks] box of each LJ work block
+  const int32_t* lj_blk_box;   // [n_lj_blocks] box of each LJ work block (group kernel: of each kGroupPad blocks)
   double* pos;
   double* vel;
   const uint8_t* type;
@@ -134,9 +153,11 @@ struct Views {
   int32_t* cnt;        // [C]
   int32_t* cell_start; // [C + 1]
   int32_t* tmp;        // [N] unordered cell lists
+  uint32_t* key;       // [N] with tmp: each entry's place along x in its cell (group kernel; else null)
   int32_t* cell_atoms; // [N] ordered cell lists
   int32_t* scell;      // [N] cell of each sorted slot
-  void* payload;       // [N] int4 fixed point (mixed) / double4 (fp64): cell-centre-relative xyz + tag
+  void* payload;       // [N] int4 fixed point (mixed) / double4 (fp64): xyz + tag, cell-centre-relative, or
+                       // for the group kernel box coordinates (modulo 2^32 in fixed point) sorted by x in a cell
   void* f_lj;          // [3N] LJ force, prec
   void* f_tot;         // [3N] total force, prec
   unsigned long long* f_acc;   // [3N] half-shell LJ force, int64 fixed point (2^-32 kcal/mol/A); zero between uses
@@ -232,6 +253,13 @@ void launch_obs_chains(const Views& v, const FFDev& ff, int b, int64_t n_chains,
 // end-to-end autocorrelation of box b: reference = store the current vectors as time zero;
 // otherwise out[b] = sum_c R_c . R_c(0) / sum_c |R_c(0)|^2 (device)
 void launch_ree(const Views& v, int b, int64_t n_chains, int chain_len, bool reference, double* out, hipStream_t s);
+
+// ---- launchers (md_group.hip): the cell path's LJ force ----
+void launch_lj_group(const Views& v, const FFDev& ff, bool fp32, bool energy, hipStream_t s);
+constexpr int kGroupPad = 16;   // a box's group blocks are padded to a multiple of this
+constexpr int kSplit = 4;       // wavefronts that share a group in boxes of few groups
+constexpr int kSplitItems = 2048;   // at most this many groups
+constexpr int kGroupHomes = 8;  // home atoms per group
 
 constexpr int kTileHomesMixed = 8;   // home atoms per pass of a mixed cell-tile wave
 

@@ -231,6 +231,13 @@ __global__ __launch_bounds__(kScanBlock) void k_scan(int32_t* __restrict__ cnt, 
   if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) cell_start[C] = offset + total;
 }
 
+// Place of x along its cell kx, increasing with x (the group kernel's order inside a cell).
+__device__ inline uint32_t cell_key(double x, const BoxDev& B, int kx) {
+  const double f = __builtin_fma(x, B.cinv[0], -(double)kx);
+  return (uint32_t)(fmin(fmax(f, 0.0), 0.999999) * 4294967296.0);
+}
+
+template <bool KEY>
 __global__ __launch_bounds__(kAtomBlock) void k_scatter(Views v, const int32_t* __restrict__ gate) {
   if (gate && *gate == 0) return;
   const int b = v.blk_box[blockIdx.x];
@@ -239,14 +246,20 @@ __global__ __launch_bounds__(kAtomBlock) void k_scatter(Views v, const int32_t* 
   const bool active = local < B.n_atoms;
   const int64_t i = (int64_t)B.atom_off + local;
   int32_t c = 0, sl = 0;
+  double x = 0.0;
   if (active) {
     c = v.cell[i];
     sl = v.slot[i];
+    if (KEY) x = v.pos[i];
   }
   // the scan has read the counts: clear them for the next binning
   for (int64_t k = (int64_t)blockIdx.x * kAtomBlock + threadIdx.x; k < v.C; k += (int64_t)gridDim.x * kAtomBlock)
     v.cnt[k] = 0;
-  if (active) v.tmp[v.cell_start[c] + sl] = (int32_t)i;
+  if (active) {
+    const int32_t at = v.cell_start[c] + sl;
+    v.tmp[at] = (int32_t)i;
+    if (KEY) v.key[at] = cell_key(x, B, cell_coord(x, B.cinv[0], B.M[0]));
+  }
 }
 
 template <typename PayT>
@@ -270,7 +283,9 @@ __device__ inline void store_payload<Pay64>(Pay64* p, int64_t dst, double rx, do
 
 constexpr int kRankBatch = 4;   // list entries read together by the rank walk
 
-template <typename PayT>
+// GROUP: the payload for the group kernel, in box coordinates and ordered by x inside each cell
+// (by index at equal keys); the cell lists stay in index order.
+template <typename PayT, bool GROUP>
 __global__ __launch_bounds__(kAtomBlock) void k_rank_payload(Views v, const int32_t* __restrict__ gate) {
   if (gate && *gate == 0) return;
   const int b = v.blk_box[blockIdx.x];
@@ -287,19 +302,39 @@ __global__ __launch_bounds__(kAtomBlock) void k_rank_payload(Views v, const int3
   const int32_t n = v.cell_start[c + 1] - s0;
   // the unordered list in batches of kRankBatch entries whose loads are in flight together;
   // entries past the end re-read the last one (atom i is in the cell, so n >= 1) and count 0
-  int rank = 0;
+  const int kx = cell_coord(x, B.cinv[0], B.M[0]);
+  const uint32_t mykey = GROUP ? cell_key(x, B, kx) : 0u;
+  int rank = 0, krank = 0;
   for (int k0 = 0; k0 < n; k0 += kRankBatch) {
     int32_t t[kRankBatch];
+    uint32_t q[kRankBatch];
 #pragma unroll
-    for (int u = 0; u < kRankBatch; ++u) t[u] = v.tmp[s0 + min(k0 + u, n - 1)];
+    for (int u = 0; u < kRankBatch; ++u) {
+      t[u] = v.tmp[s0 + min(k0 + u, n - 1)];
+      if (GROUP) q[u] = v.key[s0 + min(k0 + u, n - 1)];
+    }
 #pragma unroll
-    for (int u = 0; u < kRankBatch; ++u) rank += (k0 + u < n && t[u] < i) ? 1 : 0;
+    for (int u = 0; u < kRankBatch; ++u) {
+      const bool in = k0 + u < n, lower = t[u] < i;
+      rank += in && lower ? 1 : 0;
+      if (GROUP) krank += in && (q[u] < mykey || (q[u] == mykey && lower)) ? 1 : 0;
+    }
   }
   if (rank >= n) rank = n - 1;   // only reachable if the lists were inconsistent
+  if (krank >= n) krank = n - 1;
   const int32_t dst = s0 + rank;
   v.cell_atoms[dst] = i;
   v.scell[dst] = c;
-  const int kx = cell_coord(x, B.cinv[0], B.M[0]);
+  if constexpr (GROUP) {
+    const int32_t tag = (i << 4) | ((ty & 1) << 3) | (kx & 7);
+    PayT* p = static_cast<PayT*>(v.payload) + (s0 + krank);
+    if constexpr (std::is_same<PayT, int4>::value) {
+      *p = make_int4(fix_coord(x), fix_coord(y), fix_coord(z), tag);
+    } else {
+      *p = Pay64{x, y, z, __longlong_as_double((long long)tag)};
+    }
+    return;
+  }
   const int ky = cell_coord(y, B.cinv[1], B.M[1]);
   const int kz = cell_coord(z, B.cinv[2], B.M[2]);
   const double rx = x - ((double)kx + 0.5) * B.edge[0];
@@ -887,14 +922,21 @@ void launch_scan(const Views& v, hipStream_t s, const int32_t* gate) {
 }
 
 void launch_scatter(const Views& v, hipStream_t s, const int32_t* gate) {
-  hipLaunchKernelGGL(k_scatter, dim3(v.n_atom_blocks), dim3(kAtomBlock), 0, s, v, gate);
+  if (v.key)
+    hipLaunchKernelGGL(k_scatter<true>, dim3(v.n_atom_blocks), dim3(kAtomBlock), 0, s, v, gate);
+  else
+    hipLaunchKernelGGL(k_scatter<false>, dim3(v.n_atom_blocks), dim3(kAtomBlock), 0, s, v, gate);
 }
 
 void launch_rank_payload(const Views& v, bool fp32, hipStream_t s, const int32_t* gate) {
-  if (fp32)
-    hipLaunchKernelGGL(k_rank_payload<int4>, dim3(v.n_atom_blocks), dim3(kAtomBlock), 0, s, v, gate);
-  else
-    hipLaunchKernelGGL(k_rank_payload<Pay64>, dim3(v.n_atom_blocks), dim3(kAtomBlock), 0, s, v, gate);
+  const dim3 g(v.n_atom_blocks), blk(kAtomBlock);
+  if (v.key) {
+    if (fp32) hipLaunchKernelGGL((k_rank_payload<int4, true>), g, blk, 0, s, v, gate);
+    else hipLaunchKernelGGL((k_rank_payload<Pay64, true>), g, blk, 0, s, v, gate);
+  } else {
+    if (fp32) hipLaunchKernelGGL((k_rank_payload<int4, false>), g, blk, 0, s, v, gate);
+    else hipLaunchKernelGGL((k_rank_payload<Pay64, false>), g, blk, 0, s, v, gate);
+  }
 }
 
 template <typename P>

@@ -1,0 +1,103 @@
+"""GPU parity of the group Lennard-Jones kernel (MD_LJ_ATOM, and every FP64 cell-path kernel) where its
+branches change: one or several wavefronts per group, both in one batch, candidate lists longer than one
+chunk, groups split by their extent."""
+import numpy as np
+import pytest
+
+import oracle as O
+from pe_melt import make_melt
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"mixed": 1e-5, "fp64": 1e-10}   # max force error over the oracle's RMS force (FP32 / FP64 forces)
+
+
+def norm_err(f, ref):
+    return float(np.max(np.sqrt(np.sum((f - ref) ** 2, axis=0))) / np.sqrt(np.mean(np.sum(ref ** 2, axis=0))))
+
+
+def system(ff, melts, precision, R, kernel, **kw):
+    from paper_1001_3764_amd.md import MDSystem
+    print("system: N=%s precision=%s R=%d kernel=%d" % ([m.n_atoms for m in melts], precision, R, kernel), flush=True)
+    cat = [np.concatenate(a, axis=-1) for a in zip(*[(m.pos, m.vel, m.types) for m in melts])]
+    return MDSystem(ff, [m.n_chains for m in melts], np.stack([m.box for m in melts]), [0.0] * len(melts), *cat,
+                    chain_len=melts[0].chain_len, precision=precision, cell_div=R, lj_kernel=kernel, **kw)
+
+
+@pytest.mark.parametrize("precision,kernel", [("mixed", 1), ("fp64", 1), ("fp64", 2)])
+@pytest.mark.parametrize("chains,R", [(49, 1), (49, 2), (70, 1), (70, 2), (70, 3)])
+def test_either_side_of_the_split(ff, chains, R, precision, kernel):
+    """14,700 atoms have at most 2,048 groups (several wavefronts share one), 21,000 more (one each)."""
+    if R == 3 and kernel != 1:
+        pytest.skip("cell_div = 3 is MD_LJ_ATOM's")
+    m = make_melt(chains, density=0.80, T=500.0, seed_melt=310 + chains, seed_vel=311, jitter=0.05)
+    s = system(ff, [m], precision, R, kernel)
+    fo, eo = O.forces(ff, m.pos, m.types, m.box, 300)
+    err = norm_err(s.forces(), fo)
+    e = s.energies()[0]
+    s.close()
+    print("force error %.3e" % err)
+    assert err <= TOL[precision]
+    assert e["e_lj"] == pytest.approx(eo["e_lj"], rel=2e-6 if precision == "mixed" else 1e-12)
+
+
+@pytest.mark.parametrize("precision", ["mixed", "fp64"])
+def test_batch_of_both_kinds(ff, precision):
+    """A box on each side of the split in one context: each equals the box alone, bit for bit."""
+    melts = [make_melt(c, density=0.80, T=400.0, seed_melt=500 + c, seed_vel=501, jitter=0.05) for c in (9, 70, 12)]
+    s = system(ff, melts, precision, 2, 1)
+    s.step(3)
+    p, v = s.state()
+    e = s.energies()
+    s.close()
+    at = 0
+    for b, m in enumerate(melts):
+        a = system(ff, [m], precision, 2, 1)
+        a.step(3)
+        pa, va = a.state()
+        ea = a.energies()[0]
+        a.close()
+        assert np.array_equal(pa, p[:, at:at + m.n_atoms]) and np.array_equal(va, v[:, at:at + m.n_atoms])
+        assert ea["e_lj"] == e[b]["e_lj"] and ea["virial"] == e[b]["virial"]
+        at += m.n_atoms
+
+
+@pytest.mark.parametrize("precision", ["mixed", "fp64"])
+@pytest.mark.parametrize("R,chains", [(1, 24), (2, 24), (2, 75)])
+def test_more_than_a_chunk_of_candidates(ff, R, chains, precision):
+    """A melt squeezed to 0.55 of its box edge (6 times the density): a group's rows hold more than the
+    4,096 candidates whose run starts are marked at a time (also with one wavefront per group)."""
+    m = make_melt(chains, density=0.80, T=500.0, seed_melt=77, seed_vel=78, jitter=0.05)
+    import dataclasses
+    m = dataclasses.replace(m, pos=np.ascontiguousarray(m.pos * 0.55), box=m.box * 0.55)
+    s = system(ff, [m], precision, R, 1)
+    fo, _ = O.forces(ff, m.pos, m.types, m.box, 300)
+    err = norm_err(s.forces(), fo)
+    s.close()
+    print("force error %.3e" % err)
+    assert err <= TOL[precision]
+
+
+@pytest.mark.parametrize("precision", ["mixed", "fp64"])
+@pytest.mark.parametrize("scale", [1.0, 3.0])
+def test_sparse_rows(ff, precision, scale):
+    """Short chains spread thinly (scale stretches the box, to 209 A along x): the homes of a group lie
+    further apart than one group may extend, past the 128 A the fixed-point offsets tell apart."""
+    m = make_melt(12, chain_len=24, density=0.02, T=500.0, seed_melt=9, seed_vel=10, jitter=0.05)
+    box = m.box * np.array([scale, 1.0, 1.0])
+    pos = m.pos.copy()
+    # whole chains are moved: x of the first site stretched, the chain carried along
+    x = pos[0].reshape(12, 24)
+    d = np.diff(x, axis=1)
+    d -= m.box[0] * np.round(d / m.box[0])
+    x = x[:, :1] * scale + np.concatenate([np.zeros((12, 1)), np.cumsum(d, axis=1)], axis=1)
+    pos[0] = np.mod(x.reshape(-1), box[0])
+    import dataclasses
+    m = dataclasses.replace(m, pos=np.ascontiguousarray(pos), box=box)
+    s = system(ff, [m], precision, 2, 1)
+    fo, _ = O.forces(ff, m.pos, m.types, m.box, 24)
+    flj, _ = O.lj_brute(ff, m.pos, m.types, m.box, 24)
+    err, err_lj = norm_err(s.forces(), fo), norm_err(s.forces(lj_only=True), flj)
+    s.close()
+    print("force error %.3e, LJ %.3e" % (err, err_lj))
+    assert err <= TOL[precision] and err_lj <= TOL[precision]
