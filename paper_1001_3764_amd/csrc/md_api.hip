@@ -200,6 +200,7 @@ struct Plan {
   int prec = 0;
   int chain_len = 1;
   std::vector<BoxDev> boxes;
+  std::vector<GroupDev> groups;             // group kernel
 };
 
 // The group kernel (md_group.hip) runs MD_LJ_ATOM in both precisions and the FP64 form of the two cell
@@ -210,25 +211,27 @@ bool group_kernel(const md_config* cfg, int kernel) {
   return kernel == MD_LJ_ATOM || (cfg->precision == MD_PREC_FP64 && (kernel == MD_LJ_CELLTILE || kernel == MD_LJ_CELLTILE_NB));
 }
 
-// Work of the group kernel in a box of n atoms: lj_slots waves per row of cells, each taking every
-// lj_slots-th group of the row (a row of a melt holds its mean +- a few per cent; fuller rows give
+// Work of the group kernel in box B of n atoms: `slots` waves per row of cells, each taking every
+// slots-th group of the row (a row of a melt holds its mean +- a few per cent; fuller rows give
 // some waves a second group), on at most one block per 4 atoms (their energy partials live in the
 // bins' scratch, see carve) plus the padding.
-void group_work(const md_forcefield* ff, const md_config* cfg, int64_t n, BoxDev* B) {
-  const int64_t rows = (int64_t)B->M[1] * B->M[2];
+GroupDev group_work(const md_forcefield* ff, const md_config* cfg, int64_t n, const BoxDev& B) {
+  GroupDev g{};
+  const int64_t rows = (int64_t)B.M[1] * B.M[2];
   const double per_row = (double)n / (double)rows;
-  B->lj_slots = (int32_t)std::ceil(1.04 * per_row / kGroupHomes + 0.25);
-  B->lj_items = (int32_t)(rows * B->lj_slots);
+  g.slots = (int32_t)std::ceil(1.04 * per_row / kGroupHomes + 0.25);
+  g.items = (int32_t)(rows * g.slots);
   const int64_t most = std::max<int64_t>(n / 4, 1);
-  B->lj_blocks = (int32_t)((std::min<int64_t>(B->lj_items, most) + kGroupPad - 1) / kGroupPad * kGroupPad);
-  B->lj_waves = B->lj_items <= kSplitItems ? kSplit : 1;
-  B->inv_slots = 1.0 / (double)B->lj_slots;
-  B->inv_m1 = 1.0 / (double)B->M[1];
-  for (int d = 0; d < 3; ++d) B->L_q[d] = fix_coord(B->L[d]);
-  // a group's candidates lie within lj_cap + rc + edge of its first atom; in the mixed form that
-  // must stay below 64 A (payload_ok: (R + 2) edge < 63 A, so the cap is at least edge - 1)
-  B->lj_cap = ff->rc;
-  if (cfg->precision == MD_PREC_MIXED) B->lj_cap = std::min(ff->rc, 62.0 - ff->rc - B->edge[0]);
+  g.blocks = (int32_t)((std::min<int64_t>(g.items, most) + kGroupPad - 1) / kGroupPad * kGroupPad);
+  g.waves = g.items <= kSplitItems ? kSplit : 1;
+  g.inv_slots = 1.0 / (double)g.slots;
+  g.inv_m1 = 1.0 / (double)B.M[1];
+  for (int d = 0; d < 3; ++d) g.L_q[d] = fix_coord(B.L[d]);
+  // a group's candidates lie within cap + rc + edge of its first atom; in the mixed form that must
+  // stay below 64 A (payload_ok: (R + 2) edge < 63 A, so the cap is at least edge - 1)
+  g.cap = ff->rc;
+  if (cfg->precision == MD_PREC_MIXED) g.cap = std::min(ff->rc, 62.0 - ff->rc - B.edge[0]);
+  return g;
 }
 
 // List capacity (a list that fills up is reported as MD_ERR_NLIST).  Per-atom lists: the
@@ -300,11 +303,11 @@ Plan make_plan(const md_forcefield* ff, const md_config* cfg, int R, int kernel)
     cell += nc;
     blk += (n + kAtomBlock - 1) / kAtomBlock;
     if (p.group) {
-      group_work(ff, cfg, n, &p.boxes.emplace_back(B));
-      lblk += p.boxes.back().lj_blocks;
-      continue;
+      p.groups.push_back(group_work(ff, cfg, n, B));
+      lblk += p.groups.back().blocks;
+    } else {
+      lblk += lj_blocks_for_box(kernel, n, nc);
     }
-    lblk += lj_blocks_for_box(kernel, n, nc);
     if (nl) {
       cblk += (nc + kTileWaves - 1) / kTileWaves;
       nle += (kernel == MD_LJ_NLIST_TILE ? nc : (n + 63) / 64 * 64) * (int64_t)p.nl_cap;
@@ -354,11 +357,12 @@ size_t carve(const Plan& p, char* base, Views* v) {
   t.n_boxes = p.n_boxes;
   t.n_atom_blocks = p.n_atom_blocks;
   t.n_lj_blocks = p.n_lj_blocks;
-  for (const BoxDev& B : p.boxes) t.lj_wave_mask |= B.lj_waves == kSplit ? 2 : 1;
+  for (const GroupDev& g : p.groups) t.lj_wave_mask |= g.waves == kSplit ? 2 : 1;
   t.boxes = (const BoxDev*)take(sizeof(BoxDev) * p.n_boxes);
   t.blk_box = (const int32_t*)take(4 * (size_t)p.n_atom_blocks);
   t.lj_blk_box = (const int32_t*)take(4 * (size_t)(p.group ? p.n_lj_blocks / kGroupPad : p.n_lj_blocks));
   if (p.group) {
+    t.groups = (const GroupDev*)take(sizeof(GroupDev) * p.n_boxes);
     // one scratch area for what never lives at the same time: the bins' working arrays (from the
     // count to the rank), the LJ energy partials (from the force kernel to the reduction) and the
     // observables' block partials
@@ -510,6 +514,9 @@ md_status configure(md_ctx* c, const md_config* cfg, int R, int kernel) {
   if ((st = hip_check(c, hipStreamSynchronize(c->stream), "sync"))) return st;
   if ((st = hip_check(c, hipMemcpy((void*)v.boxes, p.boxes.data(), sizeof(BoxDev) * p.n_boxes,
                                    hipMemcpyHostToDevice), "upload boxes")))
+    return st;
+  if (p.group && (st = hip_check(c, hipMemcpy((void*)v.groups, p.groups.data(), sizeof(GroupDev) * p.n_boxes,
+                                              hipMemcpyHostToDevice), "upload group work")))
     return st;
   if ((st = hip_check(c, hipMemcpy((void*)v.blk_box, bb.data(), 4 * bb.size(), hipMemcpyHostToDevice),
                       "upload block table")))
@@ -1096,7 +1103,7 @@ md_status md_observables(md_ctx* c, const md_obs_config* o, uint64_t* pairs, uin
   for (int b = 0; b < c->n_boxes; ++b) {
     const int64_t n = (int64_t)c->n_chains[b] * c->chain_len;
     if (pairs)
-      launch_obs_pairs(c->v, b, n, c->chain_len, c->ff.excl_depth, dr, o->rdf_bins,
+      launch_obs_pairs(c->v, b, c->hboxes[b].n_cells, c->chain_len, c->ff.excl_depth, dr, o->rdf_bins,
                        (unsigned long long*)pairs + (int64_t)b * o->rdf_bins, c->stream);
     if (dih)
       launch_obs_dihedrals(c->v, b, n, c->chain_len, o->dih_bins,

@@ -158,8 +158,10 @@ void k_lj_group(Views v, FFDev ff, LjPair<float> cf, LjPair<double> cd) {
   const int per_xcd = (int)gridDim.x / kXcds;
   const int blk = ((int)blockIdx.x % kXcds) * per_xcd + (int)blockIdx.x / kXcds;
   if (blk >= v.n_lj_blocks) return;
-  const BoxDev& B = v.boxes[v.lj_blk_box[blk / kGroupPad]];
-  if (B.lj_waves != NW) return;   // a box of the other launch
+  const int box = v.lj_blk_box[blk / kGroupPad];
+  const BoxDev& B = v.boxes[box];
+  const GroupDev& Q = v.groups[box];
+  if (Q.waves != NW) return;   // a box of the other launch
   const PayT* __restrict__ pay = static_cast<const PayT*>(v.payload);
   const int32_t* __restrict__ cs = v.cell_start;
   const int R = v.R, W = 2 * R + 1;
@@ -168,15 +170,15 @@ void k_lj_group(Views v, FFDev ff, LjPair<float> cf, LjPair<double> cd) {
   const int oz = (int)(((float)ln + 0.5f) * rcp_f((float)W)) - R, oy = ln - (oz + R) * W - R;
   double e = 0.0, es = 0.0, w = 0.0;
 
-  const int S = B.lj_slots, items = B.lj_items, stride = B.lj_blocks;
+  const int S = Q.slots, items = Q.items, stride = Q.blocks;
   for (int item = blk - B.lj_blk_off; item < items; item += stride) {
-    const int row = uni((int)(((double)item + 0.5) * B.inv_slots));          // item / S
-    const int kz = uni((int)(((double)row + 0.5) * B.inv_m1)), ky = row - kz * M1;
+    const int row = uni((int)(((double)item + 0.5) * Q.inv_slots));          // item / S
+    const int kz = uni((int)(((double)row + 0.5) * Q.inv_m1)), ky = row - kz * M1;
     const int row0 = B.cell_off + row * M0;
     const int rs = uni(cs[row0]), re = uni(cs[row0 + M0]);
     for (int p0 = rs + (item - row * S) * K; p0 < re; p0 += S * K) {
       const int kc = min(K, re - p0);
-      // Homes further than lj_cap along x from the group's first one start a group of their own
+      // Homes further than Q.cap along x from the group's first one start a group of their own
       // (sparse rows): the frame stays within the fixed-point range and the runs stay short.
       for (int h0 = 0, h1 = 0; h0 < kc; h0 = h1) {
         P ax[NH], ay[NH], az[NH];
@@ -199,7 +201,7 @@ void k_lj_group(Views v, FFDev ff, LjPair<float> cf, LjPair<double> cd) {
           const float fx = G::filt(ux), fy = G::filt(uy), fz = G::filt(uz);
           // (the cell distance tells apart what the offset modulo 128 A cannot)
           kx = lane_value(hcell, h0);
-          const float dx0 = (fx - G::kZero) * (1.0f / G::kUnit), e0 = (float)B.edge[0], cap = (float)B.lj_cap;
+          const float dx0 = (fx - G::kZero) * (1.0f / G::kUnit), e0 = (float)B.edge[0], cap = (float)Q.cap;
           const bool apart = (float)(hcell - kx) * e0 > cap + e0 || dx0 > cap || dx0 < -1.0f;
           const uint64_t past = __builtin_amdgcn_ballot_w64(ln > h0 && ln < kc && apart);
           h1 = past ? __ffsll((unsigned long long)past) - 1 : kc;
@@ -365,15 +367,15 @@ void k_lj_group(Views v, FFDev ff, LjPair<float> cf, LjPair<double> cd) {
           const uint64_t some = __builtin_amdgcn_ballot_w64(n > 0);
           Off sx;
           if constexpr (FP64) sx = ox0 + (double)im * B.L[0];
-          else sx = (Off)((uint32_t)ox0 + (uint32_t)im * (uint32_t)B.L_q[0]);
+          else sx = (Off)((uint32_t)ox0 + (uint32_t)im * (uint32_t)Q.L_q[0]);
           if (n > 0) {
             Run<Off> r;
             if constexpr (FP64) {
               r.oy = oy0 + (double)wy * B.L[1];
               r.oz = oz0 + (double)wz * B.L[2];
             } else {
-              r.oy = (Off)((uint32_t)oy0 + (uint32_t)wy * (uint32_t)B.L_q[1]);
-              r.oz = (Off)((uint32_t)oz0 + (uint32_t)wz * (uint32_t)B.L_q[2]);
+              r.oy = (Off)((uint32_t)oy0 + (uint32_t)wy * (uint32_t)Q.L_q[1]);
+              r.oz = (Off)((uint32_t)oz0 + (uint32_t)wz * (uint32_t)Q.L_q[2]);
             }
             r.src = start - f;
             runs[lanes_below(some)] = r;

@@ -63,15 +63,18 @@ struct BoxDev {
   double dof;             // 3N - 3
   double inv_mass;        // 1 / total mass of the box
   int64_t nl_off;         // first entry of this box's neighbour lists
-  // group kernel (md_group.hip): work items (lj_slots per row of cells) and blocks of this box
-  int32_t lj_slots, lj_items, lj_blocks;
-  int32_t lj_waves;       // wavefronts per group: 1, or kSplit in small boxes
-  int32_t L_q[3];         // edges in fixed-point units, modulo 2^32
-  double inv_slots, inv_m1;   // 1 / lj_slots, 1 / M[1]
-  double lj_cap;          // A: extent along x of a group of home atoms
   // first-level chunks of the per-box reduction (kReduceChunk block partials each)
   int32_t bd_chunk_off, bd_chunks;   // of the bonded/kinetic partials
   int32_t lj_chunk_off, lj_chunks;   // of the LJ partials (numbered after all bonded chunks)
+};
+
+// Per box, for the group kernel (md_group.hip).
+struct GroupDev {
+  int32_t slots, items, blocks;   // work items per row of cells and in all; blocks of this box
+  int32_t waves;                  // wavefronts per group: 1, or kSplit in small boxes
+  int32_t L_q[3];                 // edges in fixed-point units, modulo 2^32
+  double inv_slots, inv_m1;       // 1 / slots, 1 / M[1]
+  double cap;                     // A: extent along x of a group of home atoms
 };
 
 // Force-field constants in the form the kernels use (built on the host).
@@ -143,6 +146,7 @@ struct Views {
   int32_t n_atom_blocks, n_lj_blocks;
   int32_t lj_wave_mask;    // group kernel: bit 0 / 1: some box has one / kSplit waves per group
   const BoxDev* boxes;
+  const GroupDev* groups;      // [n_boxes] (group kernel; else null)
   const int32_t* blk_box;      // [n_atom_blocks] box of each per-atom block
   const int32_t* lj_blk_box;   // [n_lj_blocks] box of each LJ work block (group kernel: of each kGroupPad blocks)
   double* pos;
@@ -244,7 +248,7 @@ void launch_nl_integrate(const Views& v, const StepOpts& o, const FFDev& ff, boo
                          hipStream_t s);
 
 // ---- launchers (md_obs.hip): Section 5 observables of box b ----
-void launch_obs_pairs(const Views& v, int b, int64_t n_atoms, int chain_len, int excl, double dr, int n_bins,
+void launch_obs_pairs(const Views& v, int b, int64_t n_cells, int chain_len, int excl, double dr, int n_bins,
                       unsigned long long* out, hipStream_t s);
 void launch_obs_dihedrals(const Views& v, int b, int64_t n_atoms, int chain_len, int n_bins,
                           unsigned long long* out, hipStream_t s);

@@ -3,13 +3,12 @@
 // gauche fractions (Figs. 9, 15), and per-chain radius of gyration and end-to-end vector
 // (Figs. 8, 12).
 //
-//   k_obs_pairs      one lane per atom of the sorted order: its own cell (the atoms after it
-//                    in the sorted order) and the forward half of the current grid's stencil
-//                    (with at least 2R + 1 cells per dimension no pair of cells is reached from
-//                    both sides), so every unordered non-excluded pair is counted once; the
-//                    bin is decided in FP64 on r^2 against squared edges, so the counts are
-//                    exact integers; a block histogram in LDS (integer atomics: the counts
-//                    do not depend on their order), one row of block partials per block
+//   k_obs_pairs      one wavefront per cell: its atoms against the forward half of the current
+//                    grid's stencil (with at least 2R + 1 cells per dimension no pair of cells is
+//                    reached from both sides), so every unordered non-excluded pair is counted
+//                    once; the bin is decided in FP64 on r^2 against squared edges, so the
+//                    counts are exact integers; a block histogram in LDS (integer atomics: the
+//                    counts do not depend on their order), one row of block partials per block
 //   k_obs_dihedrals  one lane per dihedral: the IUPAC angle, its bin and its class
 //   k_obs_reduce     per bin, the block partials in block order (64-bit)
 //   k_obs_chains     one wavefront per chain: the chain unwrapped bond by bond (a wave
@@ -28,57 +27,168 @@ __device__ inline double mi_rn(double t, double L, double invL) {
   return __dadd_rn(t, -__dmul_rn(L, rint(__dmul_rn(t, invL))));
 }
 
-// the largest k with (k dr)^2 <= r2 (r2 below the last edge)
-__device__ inline int distance_bin(double r2, double dr, int n_bins) {
-  int k = (int)(sqrt(r2) / dr);
-  if (k > n_bins - 1) k = n_bins - 1;
-  while (k > 0 && r2 < __dmul_rn(__dmul_rn((double)k, dr), __dmul_rn((double)k, dr))) --k;
-  while (k + 1 < n_bins && r2 >= __dmul_rn(__dmul_rn((double)(k + 1), dr), __dmul_rn((double)(k + 1), dr))) ++k;
+// The largest k < n_bins with edge2[k] <= r2 (r2 below edge2[n_bins]; edge2[k] = (k dr)^2): a guess
+// from FP32 (rarely off, and then by one bin for any but absurdly small distances), then the
+// exact comparison.
+__device__ inline int distance_bin(double r2, float inv_dr, const double* edge2, int n_bins) {
+  int k = min((int)(__builtin_amdgcn_sqrtf((float)r2) * inv_dr), n_bins - 1);
+  const double lo = edge2[k], hi = edge2[k + 1];
+  if (r2 < lo || r2 >= hi) {
+    while (k > 0 && r2 < edge2[k]) --k;
+    while (k + 1 < n_bins && r2 >= edge2[k + 1]) ++k;
+  }
   return k;
 }
 
-__global__ __launch_bounds__(kAtomBlock) void k_obs_pairs(Views v, int b, int chain_len, int excl, double dr,
-                                                        int n_bins, uint32_t* part) {
-  __shared__ uint32_t hist[kMaxObsBins];
-  for (int k = (int)threadIdx.x; k < n_bins; k += kAtomBlock) hist[k] = 0;
+// Exclusive prefix sum over the wave.
+__device__ inline int wave_scan(int x, int& total) {
+  const int ln = lane();
+  int s = x;
+  for (int d = 1; d < 64; d <<= 1) {
+    const int y = __shfl_up(s, d);
+    if (ln >= d) s += y;
+  }
+  total = __builtin_amdgcn_readlane(s, 63);
+  return s - x;
+}
+
+// LDS is shared within one wavefront here, which executes its LDS accesses in order: only the
+// compiler has to keep them so.
+__device__ __forceinline__ void lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+struct alignas(16) ObsAtom {
+  double x, y, z;
+  int32_t idx, flat;   // atom; its place in the wave's candidate list (homes: in the cell)
+};
+
+// One wavefront per home cell (grid stride).  The candidates of a cell are its own atoms, then
+// the forward half of the stencil: the cells after it in its row, the rows after it in its layer
+// and the layers after it, each row one or two contiguous runs of the cell lists.  64 of them at a
+// time go to LDS with their FP64 positions (read once per cell, where a lane per atom read
+// them once per pair), and the lanes take the home-candidate pairs 64 at a time.  The
+// minimum image is evaluated only where some difference of the wave's pairs reaches 0.499 L (below
+// that it is the difference itself).  Bound: LDS (the pairs' operands, the edges and the histogram's
+// atomics) and FP64 issue, about equally.  300,000 atoms, 210 bins, R = 2: 1,200 us with a lane per
+// atom, 245 us here (12 waves per block; 8, 10 and 16: 275, 270, 310).
+constexpr int kObsWaves = 12;
+__global__ __launch_bounds__(64 * kObsWaves) void k_obs_pairs(Views v, int b, int chain_len, int excl, double dr,
+                                                            int n_bins, uint32_t* part) {
+  extern __shared__ double obs_lds[];   // edge2[n_bins + 1], hist[n_bins]
+  double* const edge2 = obs_lds;
+  uint32_t* const hist = (uint32_t*)(obs_lds + n_bins + 1);
+  __shared__ ObsAtom cands[kObsWaves][64], homes_[kObsWaves][64];
+  __shared__ int2 window_[kObsWaves][64];
+  __shared__ int32_t runs[kObsWaves][64];
+  __shared__ unsigned long long marks[kObsWaves][64];
+  for (int k = (int)threadIdx.x; k <= n_bins; k += 64 * kObsWaves) {
+    if (k < n_bins) hist[k] = 0;
+    edge2[k] = __dmul_rn(__dmul_rn((double)k, dr), __dmul_rn((double)k, dr));
+  }
   __syncthreads();
   const BoxDev& B = v.boxes[b];
   const double rmax2 = __dmul_rn(__dmul_rn((double)n_bins, dr), __dmul_rn((double)n_bins, dr));
+  const float inv_dr = (float)(1.0 / dr);
   const int64_t N = v.N;
   const int R = v.R, W = 2 * R + 1;
   const int M0 = B.M[0], M1 = B.M[1], M2 = B.M[2];
-  for (int64_t s = B.atom_off + (int64_t)blockIdx.x * kAtomBlock + threadIdx.x; s < B.atom_off + B.n_atoms;
-       s += (int64_t)gridDim.x * kAtomBlock) {
-    const int32_t i = v.cell_atoms[s];
-    const int lc = v.scell[s] - B.cell_off;
+  const int ln = lane(), wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  ObsAtom* const cand = cands[wave];
+  ObsAtom* const homes = homes_[wave];
+  int2* const window = window_[wave];
+  const double hx = 0.499 * B.L[0], hy = 0.499 * B.L[1], hz = 0.499 * B.L[2];
+  // this lane's run: 0 the home cell, 1 and 2 the rest of its row, then two per forward row (the
+  // part inside the box and the part wrapped around it); 3 + 2 (R + R W) <= 51 lanes
+  const int fr = ln < 3 ? 0 : (ln - 3) / 2, wrapped = ln < 3 ? ln == 2 : (ln - 3) & 1;
+  const int oy = ln < 3 ? 0 : (fr < R ? fr + 1 : (fr - R) % W - R), oz = ln < 3 || fr < R ? 0 : (fr - R) / W + 1;
+  const bool used = ln < 3 + 2 * (R + R * W);
+  for (int lc = (int)blockIdx.x * kObsWaves + wave; lc < B.n_cells; lc += (int)gridDim.x * kObsWaves) {
+    const int hs = v.cell_start[B.cell_off + lc], hn = v.cell_start[B.cell_off + lc + 1] - hs;
+    if (hn == 0) continue;
     const Cell3 k3 = cell_coords(lc, B);
-    const double xi = v.pos[i], yi = v.pos[N + i], zi = v.pos[2 * N + i];
-    const int32_t ci = i / chain_len;
-    const int ctr = (W * W * W - 1) / 2;   // the cell itself; codes above it are the forward half
-    for (int code = ctr; code < W * W * W; ++code) {
-      const Cell3 o = stencil_offset(code, R);
-      int nx = k3.x + o.x, ny = k3.y + o.y, nz = k3.z + o.z;
-      nx += nx < 0 ? M0 : 0;
-      nx -= nx >= M0 ? M0 : 0;
+    int n = 0, start = 0;
+    if (used) {
+      int ny = k3.y + oy, nz = k3.z + oz;
       ny += ny < 0 ? M1 : 0;
       ny -= ny >= M1 ? M1 : 0;
-      nz += nz < 0 ? M2 : 0;
       nz -= nz >= M2 ? M2 : 0;
-      const int c = B.cell_off + nx + M0 * (ny + M1 * nz);
-      const int32_t e = v.cell_start[c + 1];
-      for (int32_t t = code == ctr ? (int32_t)s + 1 : v.cell_start[c]; t < e; ++t) {
-        const int32_t j = v.cell_atoms[t];
-        if (j / chain_len == ci && abs(j - i) <= excl) continue;
-        const double dx = mi_rn(__dadd_rn(xi, -v.pos[j]), B.L[0], B.invL[0]);
-        const double dy = mi_rn(__dadd_rn(yi, -v.pos[N + j]), B.L[1], B.invL[1]);
-        const double dz = mi_rn(__dadd_rn(zi, -v.pos[2 * N + j]), B.L[2], B.invL[2]);
-        const double r2 = __dadd_rn(__dadd_rn(__dmul_rn(dx, dx), __dmul_rn(dy, dy)), __dmul_rn(dz, dz));
-        if (r2 < rmax2) atomicAdd(&hist[distance_bin(r2, dr, n_bins)], 1u);
+      const int row = B.cell_off + M0 * (ny + M1 * nz);
+      int lo = ln < 3 ? k3.x + 1 : k3.x - R, hi = k3.x + R;   // unwrapped cells of the run's row
+      if (ln == 0) lo = hi = k3.x;
+      int a = max(lo, 0), z = min(hi, M0 - 1);
+      if (wrapped) {   // (M0 >= W: at most one side leaves the box)
+        a = lo < 0 ? lo + M0 : max(lo - M0, 0);
+        z = lo < 0 ? M0 - 1 : hi - M0;
+      }
+      if (a <= z) {
+        start = v.cell_start[row + a];
+        n = v.cell_start[row + z + 1] - start;
+      }
+    }
+    int total;
+    const int f = wave_scan(n, total);
+    const uint64_t some = __builtin_amdgcn_ballot_w64(n > 0);
+    if (n > 0) runs[wave][__popcll(some & ((1ull << ln) - 1ull))] = start - f;
+    const int mark = n > 0 ? f - 1 : -1;   // a run (but the first) marks the position before it
+    for (int g0 = 0; g0 < hn; g0 += 64) {
+      const int hc = min(64, hn - g0);
+      const float inv_hc = __builtin_amdgcn_rcpf((float)hc);
+      if (ln < hc) {
+        const int32_t i = v.cell_atoms[hs + g0 + ln];
+        homes[ln] = ObsAtom{v.pos[i], v.pos[N + i], v.pos[2 * N + i], i, g0 + ln};
+        const int32_t c0 = i - i % chain_len;
+        const int32_t lo = max(i - excl, c0);
+        window[ln] = make_int2(lo, min(i + excl, c0 + chain_len - 1) - lo);
+      }
+      for (int t0 = 0; t0 < total; t0 += 64 * 64) {
+        marks[wave][ln] = 0ull;
+        lds_order();
+        const int at = mark - t0;
+        if (mark >= 0 && at >= 0 && at < 64 * 64) atomicOr(&marks[wave][at >> 6], 1ull << (at & 63));
+        lds_order();
+        const unsigned long long mk = marks[wave][ln];
+        const int end = min(total, t0 + 64 * 64);
+        for (int w0 = t0; w0 < end; w0 += 64) {
+          const int win = (w0 - t0) >> 6;
+          const int before = __popcll(__builtin_amdgcn_ballot_w64(mark >= 0 && mark < w0));
+          const int ml = __builtin_amdgcn_readlane((int)(uint32_t)mk, win);
+          const int mh = __builtin_amdgcn_readlane((int)(uint32_t)(mk >> 32), win);
+          const int r = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)mh, __builtin_amdgcn_mbcnt_lo((uint32_t)ml, (uint32_t)before));
+          const int t = w0 + ln;
+          if (t < end) {
+            const int32_t j = v.cell_atoms[t + runs[wave][r]];
+            cand[ln] = ObsAtom{v.pos[j], v.pos[N + j], v.pos[2 * N + j], j, t};
+          }
+          lds_order();
+          const int wc = min(64, end - w0);
+          // all pairs (candidate p / hc, home p % hc), 64 at a time: p < 4096, so the FP32 quotient
+          // is exact
+          for (int p0 = 0; p0 < hc * wc; p0 += 64) {
+            const int p = min(p0 + ln, hc * wc - 1);
+            const int c = (int)(((float)p + 0.5f) * inv_hc);
+            const ObsAtom h = homes[p - c * hc], q = cand[c];
+            const int2 ex = window[p - c * hc];
+            // of two atoms of the home cell, the later one is the candidate
+            const bool on = p0 + ln < hc * wc && (q.flat >= hn || q.flat > h.flat) &&
+                            (uint32_t)(q.idx - ex.x) > (uint32_t)ex.y;
+            double dx = __dadd_rn(h.x, -q.x), dy = __dadd_rn(h.y, -q.y), dz = __dadd_rn(h.z, -q.z);
+            if (__builtin_amdgcn_ballot_w64(fabs(dx) > hx || fabs(dy) > hy || fabs(dz) > hz) != 0) {
+              dx = mi_rn(dx, B.L[0], B.invL[0]);
+              dy = mi_rn(dy, B.L[1], B.invL[1]);
+              dz = mi_rn(dz, B.L[2], B.invL[2]);
+            }
+            const double r2 = __dadd_rn(__dadd_rn(__dmul_rn(dx, dx), __dmul_rn(dy, dy)), __dmul_rn(dz, dz));
+            if (on && r2 < rmax2) atomicAdd(&hist[distance_bin(r2, inv_dr, edge2, n_bins)], 1u);
+          }
+          lds_order();
+        }
       }
     }
   }
   __syncthreads();
-  for (int k = (int)threadIdx.x; k < n_bins; k += kAtomBlock) part[(int64_t)blockIdx.x * kMaxObsBins + k] = hist[k];
+  for (int k = (int)threadIdx.x; k < n_bins; k += 64 * kObsWaves) part[(int64_t)blockIdx.x * kMaxObsBins + k] = hist[k];
 }
 
 // IUPAC dihedral angle of sites (p, p+1, p+2, p+3), bonds minimum-imaged
@@ -129,12 +239,24 @@ __global__ __launch_bounds__(kAtomBlock) void k_obs_dihedrals(Views v, int b, in
   for (int k = (int)threadIdx.x; k < nb; k += kAtomBlock) part[(int64_t)blockIdx.x * kMaxObsBins + k] = hist[k];
 }
 
-__global__ __launch_bounds__(256) void k_obs_reduce(const uint32_t* part, int n_blocks, int n_bins,
-                                                   unsigned long long* out) {
-  const int k = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-  if (k >= n_bins) return;
+// 64 bins per block: wave w adds the rows w, w + 16, ... of its bins (their loads in flight
+// together), then the waves in order.  One thread per bin adding 512 rows one after the other took
+// 114 us for 210 bins.
+constexpr int kObsReduceWaves = 16;
+__global__ __launch_bounds__(64 * kObsReduceWaves) void k_obs_reduce(const uint32_t* part, int n_blocks, int n_bins,
+                                                                   unsigned long long* out) {
+  __shared__ unsigned long long sh[kObsReduceWaves][64];
+  const int w = (int)threadIdx.x >> 6;
+  const int k = (int)blockIdx.x * 64 + lane();
   unsigned long long s = 0;
-  for (int q = 0; q < n_blocks; ++q) s += part[(int64_t)q * kMaxObsBins + k];
+  if (k < n_bins) {
+#pragma unroll 8
+    for (int q = w; q < n_blocks; q += kObsReduceWaves) s += part[(int64_t)q * kMaxObsBins + k];
+  }
+  sh[w][lane()] = s;
+  __syncthreads();
+  if (w != 0 || k >= n_bins) return;
+  for (int u = 1; u < kObsReduceWaves; ++u) s += sh[u][lane()];
   out[k] = s;
 }
 
@@ -237,27 +359,28 @@ __global__ __launch_bounds__(256) void k_ree(Views v, int b, int chain_len, doub
   }
 }
 
-// Box b's autocorrelation: the chain terms of k_ree summed in chain order as double-double
-// (each thread a contiguous run of chains, then the runs in thread order), out[b] = num / den.
+// Box b's autocorrelation: the chain terms of k_ree summed as double-double in a fixed order (each
+// thread every 256th chain, a butterfly over the wave, then the waves), out[b] = num / den.
 __global__ __launch_bounds__(256) void k_ree_reduce(Views v, int b, int chain_len, const double* part,
                                                     double* out) {
-  __shared__ dd sh[256][2];
+  __shared__ dd sh[4][2];
   const BoxDev& B = v.boxes[b];
   const int64_t c0 = (int64_t)B.atom_off / chain_len;
   const int64_t n = B.n_atoms / chain_len;
-  const int64_t per = (n + 255) / 256;
-  dd num = dd_from(0.0), den = dd_from(0.0);
-  for (int64_t c = (int64_t)threadIdx.x * per; c < min(n, ((int64_t)threadIdx.x + 1) * per); ++c) {
-    num = dd_add(num, dd_from(part[2 * (c0 + c)]));
-    den = dd_add(den, dd_from(part[2 * (c0 + c) + 1]));
-  }
-  sh[threadIdx.x][0] = num;
-  sh[threadIdx.x][1] = den;
+  dd s[2] = {dd_from(0.0), dd_from(0.0)};
+#pragma unroll 4
+  for (int64_t c = threadIdx.x; c < n; c += 256)
+    for (int k = 0; k < 2; ++k) s[k] = dd_add(s[k], dd_from(part[2 * (c0 + c) + k]));
+  for (int k = 0; k < 2; ++k)
+    for (int off = 32; off > 0; off >>= 1) s[k] = dd_add(s[k], dd{__shfl_xor(s[k].hi, off), __shfl_xor(s[k].lo, off)});
+  if (lane() == 0)
+    for (int k = 0; k < 2; ++k) sh[threadIdx.x >> 6][k] = s[k];
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int t = 1; t < 256; ++t) {
-      num = dd_add(num, sh[t][0]);
-      den = dd_add(den, sh[t][1]);
+    dd num = sh[0][0], den = sh[0][1];
+    for (int w = 1; w < 4; ++w) {
+      num = dd_add(num, sh[w][0]);
+      den = dd_add(den, sh[w][1]);
     }
     out[b] = (num.hi + num.lo) / (den.hi + den.lo);
   }
@@ -270,20 +393,22 @@ int obs_blocks(int64_t n) {
 
 }  // namespace
 
-void launch_obs_pairs(const Views& v, int b, int64_t n_atoms, int chain_len, int excl, double dr, int n_bins,
+void launch_obs_pairs(const Views& v, int b, int64_t n_cells, int chain_len, int excl, double dr, int n_bins,
                       unsigned long long* out, hipStream_t s) {
-  const int g = obs_blocks(n_atoms);
-  hipLaunchKernelGGL(k_obs_pairs, dim3(g), dim3(kAtomBlock), 0, s, v, b, chain_len, excl, dr, n_bins, v.obs_part);
-  hipLaunchKernelGGL(k_obs_reduce, dim3((n_bins + 255) / 256), dim3(256), 0, s, (const uint32_t*)v.obs_part, g,
-                     n_bins, out);
+  const int64_t want = (n_cells + kObsWaves - 1) / kObsWaves;
+  const int g = (int)(want > kObsBlocks ? kObsBlocks : want);
+  hipLaunchKernelGGL(k_obs_pairs, dim3(g), dim3(64 * kObsWaves),
+                     12 * (size_t)n_bins + 8, s, v, b, chain_len, excl, dr, n_bins, v.obs_part);
+  hipLaunchKernelGGL(k_obs_reduce, dim3((n_bins + 63) / 64), dim3(64 * kObsReduceWaves), 0, s,
+                     (const uint32_t*)v.obs_part, g, n_bins, out);
 }
 
 void launch_obs_dihedrals(const Views& v, int b, int64_t n_atoms, int chain_len, int n_bins,
                           unsigned long long* out, hipStream_t s) {
   const int g = obs_blocks(n_atoms);
   hipLaunchKernelGGL(k_obs_dihedrals, dim3(g), dim3(kAtomBlock), 0, s, v, b, chain_len, n_bins, v.obs_part);
-  hipLaunchKernelGGL(k_obs_reduce, dim3((n_bins + 3 + 255) / 256), dim3(256), 0, s, (const uint32_t*)v.obs_part,
-                     g, n_bins + 3, out);
+  hipLaunchKernelGGL(k_obs_reduce, dim3((n_bins + 3 + 63) / 64), dim3(64 * kObsReduceWaves), 0, s,
+                     (const uint32_t*)v.obs_part, g, n_bins + 3, out);
 }
 
 void launch_obs_chains(const Views& v, const FFDev& ff, int b, int64_t n_chains, int chain_len, double* out,

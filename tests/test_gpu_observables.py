@@ -155,3 +155,22 @@ def test_end_to_end_acf_against_the_oracle(ff):
         assert got[b] == pytest.approx(O.ree_acf(ref[:, sl], p[:, sl], m.box, m.chain_len), rel=0, abs=1e-12)
         off += m.n_atoms
     s.close()
+
+
+@pytest.mark.parametrize("R,chains", [(1, 30), (2, 30), (3, 24)])
+def test_dense_cells(ff, R, chains):
+    """A melt squeezed to half its box edge (8 times the density; R = 3: 0.6, 4.6 times): at R = 1 a cell
+    holds more than the 64 atoms taken as homes at a time and its candidates number more than the
+    4,096 whose runs are marked at a time.  Counts equal the oracle's."""
+    import dataclasses
+    m = make_melt(chains, density=0.80, T=500.0, seed_melt=61, seed_vel=62, jitter=0.05)
+    f = 0.6 if R == 3 else 0.5
+    m = dataclasses.replace(m, pos=np.ascontiguousarray(m.pos * f), box=m.box * f)
+    s = system(ff, [m], precision="mixed", cell_div=R, lj_kernel=1)
+    out = s.observables(rdf_bins=97, rdf_rmax=ff["rc"], dih_bins=0, dihedrals=False, shape=False)
+    start, _ = s.bins()
+    s.close()
+    if R == 1:
+        assert np.diff(start).max() > 64 and m.n_atoms * 14 // 27 > 4096
+    want = O.pair_histogram(m.pos, m.box, m.chain_len, ff["excl_depth"], ff["rc"], 97)
+    np.testing.assert_array_equal(out["pair_counts"][0], want)
