@@ -26,6 +26,8 @@ struct md_ctx {
   int R = 1, lj_kernel = MD_LJ_ATOM, use_graph = 0;
   int homes = 8;             // home atoms per pass of a cell-tile wave (mixed precision)
   int64_t N = 0;
+  int64_t small_lds = 0;     // > 0: every box is small (launch_small_begin), its LDS bytes
+  int64_t max_atoms = 0;     // atoms of the largest box
   FFDev ffd{};
   Views v{};
   std::vector<BoxDev> hboxes;
@@ -462,6 +464,20 @@ FFDev make_ffdev(const md_forcefield* ff, int chain_len) {
   return d;
 }
 
+// LDS bytes of the small-box kernels when every box of the plan takes them (cell path, except the FP64
+// half shell, whose payload they do not write), else 0.
+int64_t small_path(const Plan& p, int64_t* max_atoms) {
+  int64_t lds = 0;
+  *max_atoms = 0;
+  for (const BoxDev& B : p.boxes) {
+    *max_atoms = std::max<int64_t>(*max_atoms, B.n_atoms);
+    lds = std::max(lds, small_lds_bytes(B.n_atoms, B.n_cells));
+  }
+  const bool ok = !p.nl_cap && (p.group || p.prec == MD_PREC_MIXED) && !p.l1_bd && !p.l1_lj &&
+                  *max_atoms <= kSmallAtoms && lds <= kSmallLds;
+  return ok ? lds : 0;
+}
+
 md_status check_launch(md_ctx* c, const char* what) { return hip_check(c, hipGetLastError(), what); }
 
 // The end-to-end vectors of every chain: stored as the reference (reference), or correlated
@@ -574,6 +590,7 @@ md_status configure(md_ctx* c, const md_config* cfg, int R, int kernel) {
   if ((st = check_launch(c, "clear workspace"))) return st;
   c->v = v;
   c->hboxes = p.boxes;
+  c->small_lds = small_path(p, &c->max_atoms);
   c->R = R;
   c->lj_kernel = p.nl_cap && kernel != MD_LJ_NLIST_TILE ? MD_LJ_NLIST : kernel;
   c->since_build = 0;
@@ -585,6 +602,10 @@ bool nl_mode(const md_ctx* c) { return c->v.nl_cap > 0; }
 // Bins (and, in neighbour-list mode, the list) from the current positions.
 void enqueue_rebuild(md_ctx* c, hipStream_t s, bool kick) {
   const bool fp32 = c->prec == MD_PREC_MIXED;
+  if (c->small_lds) {
+    launch_small_begin(c->v, kick, opts(c), c->ffd, fp32, c->max_atoms, c->small_lds, s);
+    return;
+  }
   launch_bin_count(c->v, kick, opts(c), c->ffd, fp32, s);
   launch_scan(c->v, s);
   launch_scatter(c->v, s);
@@ -627,7 +648,13 @@ void enqueue_step(md_ctx* c, hipStream_t s, bool energy, bool force_build = fals
     enqueue_rebuild(c, s, true);
   }
   enqueue_forces(c, s, true, energy);
-  launch_reduce(c->v, energy, true, opts(c), s);
+  if (!c->small_lds) launch_reduce(c->v, energy, true, opts(c), s);   // (small boxes: the next step's first kernel)
+}
+
+// After the last step of a run: what is still pending.
+void enqueue_finish(md_ctx* c, hipStream_t s) {
+  if (c->small_lds) launch_small_end(c->v, opts(c), s);
+  else launch_finalize(c->v, opts(c), s);
 }
 
 // Neighbour-list mode with nl_every > 0: whether the next step rebuilds regardless of the
@@ -945,7 +972,7 @@ md_status md_step(md_ctx* c, int32_t n_steps) {
     }
     advance_build_counter(c, forced);
   }
-  launch_finalize(c->v, opts(c), c->stream);
+  enqueue_finish(c, c->stream);
   c->step += n_steps;
   return check_launch(c, "step");
 }

@@ -211,8 +211,9 @@ constexpr int kEnergySlots = 10; // per box: E_lj, E_lj_shifted, E_b, E_a, E_d, 
 //   v <- post * (pre * (v - u) + k dt a)
 // with k = 1/2 (velocity Verlet: pre = the pending Berendsen factor, post = 1) or k = 1
 // (leap-frog: pre = 1 - dt xi / 2, post = 1 / (1 + dt xi / 2)); u is the centre-of-mass
-// velocity still to be removed (0 unless removal is on).
-enum ThermoSlot { kThPre = 0, kThXi = 1, kThEta = 2, kThPost = 3, kThU = 4, kThermo = 8 };
+// velocity still to be removed (0 unless removal is on).  kThPending (small boxes): 1 while the sums of
+// a step are still to be reduced.
+enum ThermoSlot { kThPre = 0, kThXi = 1, kThEta = 2, kThPost = 3, kThU = 4, kThPending = 7, kThermo = 8 };
 enum Integrator { kVerletBerendsen = 0, kLeapfrogNoseHoover = 1 };
 
 // What the bonded kernel does with the velocities: nothing (forces only), the second
@@ -240,6 +241,14 @@ void launch_bonded(const Views& v, const FFDev& ff, bool fp32, BondedMode mode, 
                    double dt, hipStream_t s);
 // update: advance the integrator state (thermostat, pending COM velocity) from the sums
 void launch_reduce(const Views& v, bool energy, bool update, const StepOpts& o, hipStream_t s);
+// small boxes (one work-group per box): the first kernel of a step (kick) or of a bin rebuild, and
+// the last kernel of a run of steps (reduction with the energies, launch_finalize)
+constexpr int64_t kSmallAtoms = 4096;      // largest box that takes them
+constexpr int64_t kSmallLds = 96 << 10;     // and its LDS
+int64_t small_lds_bytes(int64_t n_atoms, int64_t n_cells);
+void launch_small_begin(const Views& v, bool kick, const StepOpts& o, const FFDev& ff, bool fp32, int64_t max_atoms,
+                        int64_t lds, hipStream_t s);
+void launch_small_end(const Views& v, const StepOpts& o, hipStream_t s);
 // applies what is pending (Berendsen factor, COM velocity) to the velocities
 void launch_finalize(const Views& v, const StepOpts& o, hipStream_t s);
 // neighbour-list mode: update + displacement check (raises nl_flag past half the skin, or always

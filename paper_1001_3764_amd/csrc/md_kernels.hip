@@ -62,6 +62,13 @@ __device__ inline Kick load_kick(const Views& v, int b) {
   return Kick{t[kThPre], t[kThPost], t[kThU], t[kThU + 1], t[kThU + 2]};
 }
 
+// v and x of one component after the kick and the drift, the same rounding in every kernel that
+// moves atoms (h = k dt a / F).
+__device__ __forceinline__ double kick_v(double v, double u, const Kick& q, double h, double f) {
+  return q.post * __builtin_fma(h, f, q.pre * (v - u));
+}
+__device__ __forceinline__ double drift_x(double x, double dt, double v) { return __builtin_fma(dt, v, x); }
+
 // Slot of this lane's atom inside its cell.  Lanes are grouped by cell in a loop with
 // no memory access (one ballot per distinct cell); then the first lane of every group adds
 // the group's size to the cell's count, all groups in one atomic instruction (one round
@@ -108,15 +115,15 @@ __global__ __launch_bounds__(kAtomBlock) void k_bin_count(Views v, const F* __re
     if (KICK) {
       const Kick q = load_kick(v, b);
       const double h = kdt * ff.acc_over_m[v.type[i]];
-      const double vx = q.post * (q.pre * (v.vel[i] - q.ux) + h * (double)f[i]);
-      const double vy = q.post * (q.pre * (v.vel[N + i] - q.uy) + h * (double)f[N + i]);
-      const double vz = q.post * (q.pre * (v.vel[2 * N + i] - q.uz) + h * (double)f[2 * N + i]);
+      const double vx = kick_v(v.vel[i], q.ux, q, h, (double)f[i]);
+      const double vy = kick_v(v.vel[N + i], q.uy, q, h, (double)f[N + i]);
+      const double vz = kick_v(v.vel[2 * N + i], q.uz, q, h, (double)f[2 * N + i]);
       v.vel[i] = vx;
       v.vel[N + i] = vy;
       v.vel[2 * N + i] = vz;
-      x += dt * vx;
-      y += dt * vy;
-      z += dt * vz;
+      x = drift_x(x, dt, vx);
+      y = drift_x(y, dt, vy);
+      z = drift_x(z, dt, vz);
       moved = true;
     }
     if (!(isfinite(x) && isfinite(y) && isfinite(z))) {
@@ -281,7 +288,24 @@ __device__ inline void store_payload<Pay64>(Pay64* p, int64_t dst, double rx, do
   p[dst] = q;
 }
 
-constexpr int kRankBatch = 4;   // list entries read together by the rank walk
+// x relative to the centre of its cell k
+__device__ __forceinline__ double rel_coord(double x, int k, double edge) {
+  return __builtin_fma(-((double)k + 0.5), edge, x);
+}
+
+__device__ __forceinline__ int32_t atom_tag(int32_t i, int32_t ty, int kx) { return (i << 4) | ((ty & 1) << 3) | (kx & 7); }
+
+// The group kernel's payload: box coordinates.
+template <typename PayT>
+__device__ __forceinline__ void group_payload(PayT* p, int64_t dst, double x, double y, double z, int32_t tag) {
+  if constexpr (std::is_same<PayT, int4>::value)
+    p[dst] = make_int4(fix_coord(x), fix_coord(y), fix_coord(z), tag);
+  else
+    p[dst] = Pay64{x, y, z, __longlong_as_double((long long)tag)};
+}
+
+constexpr int kRankBatch = 6;   // list entries read together by the rank walk (4, 8 and 16: 0.2, 0.4 and 2 us
+                                // more at 300,000 atoms, R = 2; R = 1: 4 takes 1.2 us more at 36,720)
 
 // GROUP: the payload for the group kernel, in box coordinates and ordered by x inside each cell
 // (by index at equal keys); the cell lists stay in index order.
@@ -300,47 +324,44 @@ __global__ __launch_bounds__(kAtomBlock) void k_rank_payload(Views v, const int3
   const int32_t c = v.cell[i];
   const int32_t s0 = v.cell_start[c];
   const int32_t n = v.cell_start[c + 1] - s0;
-  // the unordered list in batches of kRankBatch entries whose loads are in flight together;
-  // entries past the end re-read the last one (atom i is in the cell, so n >= 1) and count 0
+  // the unordered list in batches of kRankBatch entries whose loads are in flight together; in the
+  // last one entries past the end re-read the last entry (atom i is in the cell, so n >= 1) and
+  // count 0
   const int kx = cell_coord(x, B.cinv[0], B.M[0]);
   const uint32_t mykey = GROUP ? cell_key(x, B, kx) : 0u;
   int rank = 0, krank = 0;
-  for (int k0 = 0; k0 < n; k0 += kRankBatch) {
+  auto batch = [&](int k0, auto whole) {
     int32_t t[kRankBatch];
     uint32_t q[kRankBatch];
 #pragma unroll
     for (int u = 0; u < kRankBatch; ++u) {
-      t[u] = v.tmp[s0 + min(k0 + u, n - 1)];
-      if (GROUP) q[u] = v.key[s0 + min(k0 + u, n - 1)];
+      const int at = s0 + (decltype(whole)::value ? k0 + u : min(k0 + u, n - 1));
+      t[u] = v.tmp[at];
+      if (GROUP) q[u] = v.key[at];
     }
 #pragma unroll
     for (int u = 0; u < kRankBatch; ++u) {
-      const bool in = k0 + u < n, lower = t[u] < i;
+      const bool in = decltype(whole)::value || k0 + u < n, lower = t[u] < i;
       rank += in && lower ? 1 : 0;
       if (GROUP) krank += in && (q[u] < mykey || (q[u] == mykey && lower)) ? 1 : 0;
     }
-  }
+  };
+  int k0 = 0;
+  for (; k0 + kRankBatch <= n; k0 += kRankBatch) batch(k0, std::true_type());
+  if (k0 < n) batch(k0, std::false_type());
   if (rank >= n) rank = n - 1;   // only reachable if the lists were inconsistent
   if (krank >= n) krank = n - 1;
   const int32_t dst = s0 + rank;
   v.cell_atoms[dst] = i;
   v.scell[dst] = c;
   if constexpr (GROUP) {
-    const int32_t tag = (i << 4) | ((ty & 1) << 3) | (kx & 7);
-    PayT* p = static_cast<PayT*>(v.payload) + (s0 + krank);
-    if constexpr (std::is_same<PayT, int4>::value) {
-      *p = make_int4(fix_coord(x), fix_coord(y), fix_coord(z), tag);
-    } else {
-      *p = Pay64{x, y, z, __longlong_as_double((long long)tag)};
-    }
+    group_payload<PayT>(static_cast<PayT*>(v.payload), s0 + krank, x, y, z, atom_tag(i, ty, kx));
     return;
   }
   const int ky = cell_coord(y, B.cinv[1], B.M[1]);
   const int kz = cell_coord(z, B.cinv[2], B.M[2]);
-  const double rx = x - ((double)kx + 0.5) * B.edge[0];
-  const double ry = y - ((double)ky + 0.5) * B.edge[1];
-  const double rz = z - ((double)kz + 0.5) * B.edge[2];
-  const int32_t tag = (i << 4) | ((ty & 1) << 3) | (kx & 7);
+  const double rx = rel_coord(x, kx, B.edge[0]), ry = rel_coord(y, ky, B.edge[1]), rz = rel_coord(z, kz, B.edge[2]);
+  const int32_t tag = atom_tag(i, ty, kx);
   store_payload<PayT>(static_cast<PayT*>(v.payload), dst, rx, ry, rz, tag);
   if (v.nl_cap) {   // neighbour-list mode: where the list build saw the atom; the current payload
     store_payload<PayT>(static_cast<PayT*>(v.pay_cur), dst, rx, ry, rz, tag);   // is the build's
@@ -391,13 +412,13 @@ __global__ __launch_bounds__(kAtomBlock) void k_nl_integrate(Views v, const F* _
   const int64_t i = (int64_t)B.atom_off + local;
   const Kick q = load_kick(v, b);
   const double h = kdt * ff.acc_over_m[v.type[i]];
-  const double vx = q.post * (q.pre * (v.vel[i] - q.ux) + h * (double)f[i]);
-  const double vy = q.post * (q.pre * (v.vel[N + i] - q.uy) + h * (double)f[N + i]);
-  const double vz = q.post * (q.pre * (v.vel[2 * N + i] - q.uz) + h * (double)f[2 * N + i]);
+  const double vx = kick_v(v.vel[i], q.ux, q, h, (double)f[i]);
+  const double vy = kick_v(v.vel[N + i], q.uy, q, h, (double)f[N + i]);
+  const double vz = kick_v(v.vel[2 * N + i], q.uz, q, h, (double)f[2 * N + i]);
   v.vel[i] = vx;
   v.vel[N + i] = vy;
   v.vel[2 * N + i] = vz;
-  double x = v.pos[i] + dt * vx, y = v.pos[N + i] + dt * vy, z = v.pos[2 * N + i] + dt * vz;
+  double x = drift_x(v.pos[i], dt, vx), y = drift_x(v.pos[N + i], dt, vy), z = drift_x(v.pos[2 * N + i], dt, vz);
   if (!(isfinite(x) && isfinite(y) && isfinite(z))) {
     atomicOr(v.err, (int)kErrNonFinite);
     x = y = z = 0.0;
@@ -667,21 +688,23 @@ __global__ __launch_bounds__(bonded_threads<P>()) void k_bonded(Views v, FFDev f
   }
 }
 
-// Sums NV double-double values over the block in a fixed order (each thread's own values,
+// Sums NV double-double values over the block's first four waves in a fixed order (each thread's own values,
 // then a butterfly over the wave, then the waves in order); every thread gets the sums.
 template <int NV>
 __device__ void block_sums(dd (&s)[NV], dd (*sh)[NV]) {
-  for (int k = 0; k < NV; ++k)
-    for (int off = 32; off > 0; off >>= 1) {
-      dd o{__shfl_xor(s[k].hi, off), __shfl_xor(s[k].lo, off)};
-      s[k] = dd_add(s[k], o);
-    }
-  if (lane() == 0)
-    for (int k = 0; k < NV; ++k) sh[threadIdx.x >> 6][k] = s[k];
+  if (threadIdx.x < 256) {
+    for (int k = 0; k < NV; ++k)
+      for (int off = 32; off > 0; off >>= 1) {
+        dd o{__shfl_xor(s[k].hi, off), __shfl_xor(s[k].lo, off)};
+        s[k] = dd_add(s[k], o);
+      }
+    if (lane() == 0)
+      for (int k = 0; k < NV; ++k) sh[threadIdx.x >> 6][k] = s[k];
+  }
   __syncthreads();
   for (int k = 0; k < NV; ++k) {
     dd r = sh[0][k];
-    for (int w = 1; w < (int)(blockDim.x >> 6); ++w) r = dd_add(r, sh[w][k]);
+    for (int w = 1; w < 4; ++w) r = dd_add(r, sh[w][k]);
     s[k] = r;
   }
   __syncthreads();
@@ -741,13 +764,20 @@ __global__ __launch_bounds__(256) void k_reduce_l1(Views v, int first_chunk) {
 // ENERGY: the energies and virial too; COM (with update): the momentum and u.
 // Neighbour-list mode, with update: the step's rebuild flag has been read by every kernel
 // that uses it, so it is counted and cleared here for the next step.
+// Threads past the 256th of a larger work-group only take part in the barriers, so the sums do not
+// depend on the work-group's size.
+constexpr int kReduceThreads = 256;
+template <bool COM, bool ENERGY>
+constexpr int reduce_values() { return (COM ? 4 : 1) + (ENERGY ? 7 : 0); }
 template <bool ENERGY, bool COM>
-__global__ __launch_bounds__(256) void k_reduce(Views v, int update, StepOpts o, int l1_bd, int l1_lj) {
+__device__ __forceinline__ void reduce_box(const Views& v, int b, int update, const StepOpts& o, int l1_bd, int l1_lj,
+                                           dd (*sh)[reduce_values<COM, ENERGY>()]) {
+#pragma clang fp contract(off)
   // q: KE, [momentum xyz], [E_b E_a E_d W_b E_lj E_lj_shifted W_lj]
-  constexpr int iP = 1, iE = COM ? 4 : 1, NV = iE + (ENERGY ? 7 : 0);
-  __shared__ dd sh[4][NV];
-  const int b = blockIdx.x;
-  if (update && v.nl_flag && b == 0 && threadIdx.x == 0 && *v.nl_flag) {
+  constexpr int iP = 1, iE = COM ? 4 : 1, NV = reduce_values<COM, ENERGY>();
+  const int tid = threadIdx.x, none = 1 << 30;
+  const int t_first = tid < kReduceThreads ? tid : none;
+  if (update && v.nl_flag && b == 0 && tid == 0 && *v.nl_flag) {
     *v.nl_builds += 1ull;
     *v.nl_flag = 0;
   }
@@ -762,15 +792,15 @@ __global__ __launch_bounds__(256) void k_reduce(Views v, int update, StepOpts o,
   constexpr int NB = iE + (ENERGY ? 4 : 0);   // bonded partials read per work-group
   constexpr int kBatch = NB <= 4 ? 8 : 4;
   if (l1_bd) {
-    for (int t = threadIdx.x; t < B.bd_chunks; t += blockDim.x)
+    for (int t = t_first; t < B.bd_chunks; t += kReduceThreads)
       for (int k = 0; k < NB; ++k) q[k] = dd_add(q[k], v.part_l1[(int64_t)(B.bd_chunk_off + t) * kBdParts + k]);
   }
-  for (int t0 = threadIdx.x; !l1_bd && t0 < count; t0 += blockDim.x * kBatch) {
+  for (int t0 = t_first; !l1_bd && t0 < count; t0 += kReduceThreads * kBatch) {
     dd r[kBatch][NB];
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
       // partial k of block j at part_bd[k * n_atom_blocks + j]: consecutive lanes, consecutive blocks
-      const dd* p = v.part_bd + first + min(t0 + u * (int)blockDim.x, count - 1);
+      const dd* p = v.part_bd + first + min(t0 + u * kReduceThreads, count - 1);
       const int64_t nb = v.n_atom_blocks;
       r[u][0] = p[4 * nb];
       if (COM)
@@ -780,18 +810,18 @@ __global__ __launch_bounds__(256) void k_reduce(Views v, int update, StepOpts o,
     }
 #pragma unroll
     for (int u = 0; u < kBatch; ++u)
-      if (t0 + u * (int)blockDim.x < count)
+      if (t0 + u * kReduceThreads < count)
         for (int k = 0; k < NB; ++k) q[k] = dd_add(q[k], r[u][k]);
   }
   if (ENERGY) {
     if (l1_lj) {
-      for (int t = threadIdx.x; t < B.lj_chunks; t += blockDim.x)
+      for (int t = t_first; t < B.lj_chunks; t += kReduceThreads)
         for (int k = 0; k < 3; ++k)
           q[iE + 4 + k] = dd_add(q[iE + 4 + k], v.part_l1[(int64_t)(B.lj_chunk_off + t) * kBdParts + k]);
     } else {
       const int lfirst = B.lj_blk_off;
       const int lcount = (b + 1 < v.n_boxes ? v.boxes[b + 1].lj_blk_off : v.n_lj_blocks) - lfirst;
-      for (int t = threadIdx.x; t < lcount; t += blockDim.x)
+      for (int t = t_first; t < lcount; t += kReduceThreads)
         for (int k = 0; k < 3; ++k) q[iE + 4 + k] = dd_add(q[iE + 4 + k], v.part_lj[(int64_t)(lfirst + t) * 3 + k]);
     }
   }
@@ -808,7 +838,7 @@ __global__ __launch_bounds__(256) void k_reduce(Views v, int update, StepOpts o,
   }
   const double T = 2.0 * KE / (B.dof * kRgas);
   double* out = v.energy + (int64_t)b * kEnergySlots;
-  if (threadIdx.x != 0) return;
+  if (tid != 0) return;
   if (ENERGY) {
     out[0] = q[iE + 4].hi + q[iE + 4].lo;
     out[1] = q[iE + 5].hi + q[iE + 5].lo;
@@ -845,6 +875,12 @@ __global__ __launch_bounds__(256) void k_reduce(Views v, int update, StepOpts o,
   out[9] = lf && B.T0 > 0.0 ? B.dof * kRgas * B.T0 * (xi * xi / (2.0 * w2) + th[kThEta]) : 0.0;
 }
 
+template <bool ENERGY, bool COM>
+__global__ __launch_bounds__(kReduceThreads) void k_reduce(Views v, int update, StepOpts o, int l1_bd, int l1_lj) {
+  __shared__ dd sh[kReduceThreads / 64][reduce_values<COM, ENERGY>()];
+  reduce_box<ENERGY, COM>(v, blockIdx.x, update, o, l1_bd, l1_lj, sh);
+}
+
 // Applies the pending Berendsen factor (velocity Verlet) and COM velocity to v.
 __global__ __launch_bounds__(kAtomBlock) void k_finalize(Views v, int lf) {
   const int b = v.blk_box[blockIdx.x];
@@ -866,6 +902,206 @@ __global__ void k_clear_pending(double* thermo, int n_boxes, int lf) {
     double* th = thermo + (int64_t)b * kThermo;
     if (!lf) th[kThPre] = 1.0;
     th[kThU] = th[kThU + 1] = th[kThU + 2] = 0.0;
+  }
+}
+
+// ---- small boxes ----
+// In a box of a few thousand atoms each of a step's kernels takes the few microseconds of its chain of
+// dependent loads and the launch, not the time of its work, so one work-group per box does the
+// binning, and the reduction of a step is done by the next step's first kernel: a step is this
+// kernel, the LJ force and the bonded kernel (three launches for eight).  Same arithmetic and same
+// orders as the kernels above, so the results are theirs bit for bit.  One CU moves a box's ~200 B
+// per atom and ranks its cells, so it pays only up to a few thousand atoms: per step, mixed, R = 2,
+// 36.7 against 40.4 us at 3,000 atoms (FP64, R = 1: 44 against 55 us at 1,800), even at 4,200 and
+// 47 against 42 us at 6,000; the line is at 4,096.
+//   k_small_begin  the pending reduction (thermo slot kThPending), update, drift, wrap, cell counts in
+//                  LDS, scan, cell lists in LDS, ranks, ordered lists and payload
+//   k_small_end    after the last step of a call: the reduction with the energies, what is pending
+//                  applied to the velocities
+constexpr int kSmallThreads = 1024;
+constexpr int kSmallBits = 12;   // an entry: place along x (32 bits), cell (20), atom of the box (12)
+static_assert(kSmallAtoms <= 1 << kSmallBits && kSmallLds / 4 < 1 << (32 - kSmallBits), "entry fields");
+
+template <typename F, typename PayT, bool GROUP, bool KICK, bool COM, int PER>
+__global__ __launch_bounds__(kSmallThreads) void k_small_begin(Views v, const F* __restrict__ f, double dt, double kdt,
+                                                               FFDev ff, StepOpts o) {
+  extern __shared__ uint64_t small_lds[];   // entry[n], starts[C + 1]
+  __shared__ dd sh[kReduceThreads / 64][reduce_values<COM, false>()];
+  __shared__ int scan_sh[33];
+  const int b = blockIdx.x;
+  const BoxDev B = v.boxes[b];
+  const int tid = threadIdx.x, C = B.n_cells, n = B.n_atoms;
+  uint64_t* const entry = small_lds;   // unordered cell lists
+  int32_t* const starts = (int32_t*)(entry + n);
+  const int64_t N = v.N;
+  double* const th = v.thermo + (int64_t)b * kThermo;
+  // every load of this thread's atoms goes first, so that they are in flight together and during
+  // the reduction
+  double x[PER], y[PER], z[PER], vx[PER], vy[PER], vz[PER];
+  F fx[PER], fy[PER], fz[PER];
+  uint8_t ty[PER];
+  int32_t cell[PER], slot[PER];
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int64_t i = (int64_t)B.atom_off + min(tid + u * kSmallThreads, n - 1);
+    x[u] = v.pos[i];
+    y[u] = v.pos[N + i];
+    z[u] = v.pos[2 * N + i];
+    ty[u] = v.type[i];
+    if (KICK) {
+      vx[u] = v.vel[i];
+      vy[u] = v.vel[N + i];
+      vz[u] = v.vel[2 * N + i];
+      fx[u] = f[i];
+      fy[u] = f[N + i];
+      fz[u] = f[2 * N + i];
+    }
+  }
+  for (int c = tid; c <= C; c += kSmallThreads) starts[c] = 0;
+  if (KICK) {
+    // (the same value on every thread, read before thread 0 changes it)
+    const bool pending = th[kThPending] != 0.0;
+    __syncthreads();
+    if (pending) reduce_box<false, COM>(v, b, 1, o, 0, 0, sh);
+    if (tid == 0) th[kThPending] = 1.0;   // the step that begins here
+  }
+  __syncthreads();
+  const Kick q = load_kick(v, b);
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int t = tid + u * kSmallThreads;
+    if (t >= n) continue;
+    const int64_t i = (int64_t)B.atom_off + t;
+    bool moved = false;
+    if (KICK) {
+      const double h = kdt * ff.acc_over_m[ty[u]];
+      vx[u] = kick_v(vx[u], q.ux, q, h, (double)fx[u]);
+      vy[u] = kick_v(vy[u], q.uy, q, h, (double)fy[u]);
+      vz[u] = kick_v(vz[u], q.uz, q, h, (double)fz[u]);
+      v.vel[i] = vx[u];
+      v.vel[N + i] = vy[u];
+      v.vel[2 * N + i] = vz[u];
+      x[u] = drift_x(x[u], dt, vx[u]);
+      y[u] = drift_x(y[u], dt, vy[u]);
+      z[u] = drift_x(z[u], dt, vz[u]);
+      moved = true;
+    }
+    if (!(isfinite(x[u]) && isfinite(y[u]) && isfinite(z[u]))) {
+      atomicOr(v.err, (int)kErrNonFinite);
+      x[u] = y[u] = z[u] = 0.0;   // keep every index in range; the run is already invalid
+      moved = true;
+    }
+    const double wx = wrap_coord(x[u], B.L[0], B.invL[0]);
+    const double wy = wrap_coord(y[u], B.L[1], B.invL[1]);
+    const double wz = wrap_coord(z[u], B.L[2], B.invL[2]);
+    if (moved || wx != x[u] || wy != y[u] || wz != z[u]) {
+      v.pos[i] = wx;
+      v.pos[N + i] = wy;
+      v.pos[2 * N + i] = wz;
+    }
+    x[u] = wx;
+    y[u] = wy;
+    z[u] = wz;
+    cell[u] = cell_coord(wx, B.cinv[0], B.M[0]) +
+              B.M[0] * (cell_coord(wy, B.cinv[1], B.M[1]) + B.M[1] * cell_coord(wz, B.cinv[2], B.M[2]));
+    slot[u] = atomicAdd(&starts[cell[u]], 1);
+  }
+  __syncthreads();
+  // exclusive scan of the counts, in place: each thread a contiguous run of cells
+  {
+    const int per = (C + kSmallThreads - 1) / kSmallThreads, c0 = min(tid * per, C), c1 = min(c0 + per, C);
+    int sum = 0;
+    for (int c = c0; c < c1; ++c) sum += starts[c];
+    int total;
+    int ex = block_exclusive_scan(sum, scan_sh, &total);
+    for (int c = c0; c < c1; ++c) {
+      const int k = starts[c];
+      starts[c] = ex;
+      v.cell_start[B.cell_off + c] = B.atom_off + ex;
+      ex += k;
+    }
+    if (tid == 0) starts[C] = n;
+    if (tid == 0 && b == v.n_boxes - 1) v.cell_start[v.C] = (int32_t)N;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int t = tid + u * kSmallThreads;
+    if (t >= n) continue;
+    const uint32_t key = GROUP ? cell_key(x[u], B, cell_coord(x[u], B.cinv[0], B.M[0])) : 0u;
+    entry[starts[cell[u]] + slot[u]] = ((uint64_t)key << 32) | ((uint32_t)cell[u] << kSmallBits) | (uint32_t)t;
+  }
+  __syncthreads();
+  // the ranks, a thread per entry: the lanes of a wave then mostly read the same cell's entries (one
+  // LDS access for all of them; a thread per atom read 64 cells at once and took twice as long)
+  // and write neighbouring places
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int e = tid + u * kSmallThreads;
+    if (e >= n) continue;
+    const uint64_t mine = entry[e];
+    const uint32_t t = (uint32_t)mine & ((1u << kSmallBits) - 1u), c = (uint32_t)mine >> kSmallBits;
+    const int32_t i = B.atom_off + (int32_t)t;
+    const double px = v.pos[i], py = v.pos[N + i], pz = v.pos[2 * N + i];
+    const int32_t type = v.type[i];
+    const int s0 = starts[c], m = starts[c + 1] - s0;
+    int rank = 0, krank = 0, k0 = 0;
+    for (; k0 + 8 <= m; k0 += 8) {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const uint64_t w = entry[s0 + k0 + k];
+        rank += (uint32_t)w < (uint32_t)mine ? 1 : 0;   // (one cell: the atoms' order)
+        if (GROUP) krank += w < mine ? 1 : 0;
+      }
+    }
+    if (k0 < m) {   // the last ones: past the end the last is read again and counts nothing
+      uint64_t w[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) w[k] = entry[s0 + min(k0 + k, m - 1)];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        rank += k0 + k < m && (uint32_t)w[k] < (uint32_t)mine ? 1 : 0;
+        if (GROUP) krank += k0 + k < m && w[k] < mine ? 1 : 0;
+      }
+    }
+    const int32_t dst = B.atom_off + s0 + rank, kdst = B.atom_off + s0 + krank;
+    v.cell_atoms[dst] = i;
+    v.scell[dst] = B.cell_off + (int32_t)c;
+    const int kx = cell_coord(px, B.cinv[0], B.M[0]);
+    const int32_t tag = atom_tag(i, type, kx);
+    if constexpr (GROUP) {
+      group_payload<PayT>(static_cast<PayT*>(v.payload), kdst, px, py, pz, tag);
+    } else {
+      const int ky = cell_coord(py, B.cinv[1], B.M[1]), kz = cell_coord(pz, B.cinv[2], B.M[2]);
+      store_payload<PayT>(static_cast<PayT*>(v.payload), dst, rel_coord(px, kx, B.edge[0]),
+                          rel_coord(py, ky, B.edge[1]), rel_coord(pz, kz, B.edge[2]), tag);
+    }
+  }
+}
+
+template <bool COM>
+__global__ __launch_bounds__(kSmallThreads) void k_small_end(Views v, StepOpts o) {
+  __shared__ dd sh[kReduceThreads / 64][reduce_values<COM, true>()];
+  const int b = blockIdx.x;
+  reduce_box<true, COM>(v, b, 1, o, 0, 0, sh);
+  __syncthreads();
+  const BoxDev B = v.boxes[b];
+  double* const th = v.thermo + (int64_t)b * kThermo;
+  const bool lf = o.integrator == kLeapfrogNoseHoover;
+  const double s = lf ? 1.0 : th[kThPre];
+  const double u0 = th[kThU], u1 = th[kThU + 1], u2 = th[kThU + 2];
+  const int64_t N = v.N;
+  for (int t = threadIdx.x; t < B.n_atoms; t += kSmallThreads) {
+    const int64_t i = (int64_t)B.atom_off + t;
+    v.vel[i] = s * (v.vel[i] - u0);
+    v.vel[N + i] = s * (v.vel[N + i] - u1);
+    v.vel[2 * N + i] = s * (v.vel[2 * N + i] - u2);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    if (!lf) th[kThPre] = 1.0;
+    th[kThU] = th[kThU + 1] = th[kThU + 2] = 0.0;
+    th[kThPending] = 0.0;
   }
 }
 
@@ -998,6 +1234,43 @@ void launch_nl_integrate(const Views& v, const StepOpts& o, const FFDev& ff, boo
     hipLaunchKernelGGL((k_nl_integrate<float, int4>), g, blk, 0, s, v, (const float*)v.f_tot, o.dt, kdt, ff, fb);
   else
     hipLaunchKernelGGL((k_nl_integrate<double, Pay64>), g, blk, 0, s, v, (const double*)v.f_tot, o.dt, kdt, ff, fb);
+}
+
+int64_t small_lds_bytes(int64_t n_atoms, int64_t n_cells) { return 8 * n_atoms + 4 * (n_cells + 1); }
+
+template <typename F, typename PayT, bool GROUP, bool KICK>
+void launch_small_k(const Views& v, const StepOpts& o, const FFDev& ff, int64_t max_atoms, int64_t lds, hipStream_t s) {
+  const dim3 g(v.n_boxes), blk(kSmallThreads);
+  const double kdt = kick_dt(o);
+  const F* f = (const F*)v.f_tot;
+#define MDK_SMALL(COM, PER) \
+  hipLaunchKernelGGL((k_small_begin<F, PayT, GROUP, KICK, COM, PER>), g, blk, lds, s, v, f, o.dt, kdt, ff, o)
+  const bool com = KICK && o.remove_com;
+  if (max_atoms <= 2 * kSmallThreads) {
+    if (com) MDK_SMALL(true, 2);
+    else MDK_SMALL(false, 2);
+  } else {
+    if (com) MDK_SMALL(true, 4);
+    else MDK_SMALL(false, 4);
+  }
+#undef MDK_SMALL
+}
+
+void launch_small_begin(const Views& v, bool kick, const StepOpts& o, const FFDev& ff, bool fp32, int64_t max_atoms,
+                        int64_t lds, hipStream_t s) {
+  const bool group = v.key != nullptr;
+  if (fp32) {
+    if (group) { if (kick) launch_small_k<float, int4, true, true>(v, o, ff, max_atoms, lds, s); else launch_small_k<float, int4, true, false>(v, o, ff, max_atoms, lds, s); }
+    else { if (kick) launch_small_k<float, int4, false, true>(v, o, ff, max_atoms, lds, s); else launch_small_k<float, int4, false, false>(v, o, ff, max_atoms, lds, s); }
+  } else {   // (every FP64 cell path but the half shell is the group kernel's)
+    if (kick) launch_small_k<double, Pay64, true, true>(v, o, ff, max_atoms, lds, s);
+    else launch_small_k<double, Pay64, true, false>(v, o, ff, max_atoms, lds, s);
+  }
+}
+
+void launch_small_end(const Views& v, const StepOpts& o, hipStream_t s) {
+  if (o.remove_com) hipLaunchKernelGGL(k_small_end<true>, dim3(v.n_boxes), dim3(kSmallThreads), 0, s, v, o);
+  else hipLaunchKernelGGL(k_small_end<false>, dim3(v.n_boxes), dim3(kSmallThreads), 0, s, v, o);
 }
 
 void launch_finalize(const Views& v, const StepOpts& o, hipStream_t s) {
