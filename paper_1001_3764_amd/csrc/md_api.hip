@@ -16,6 +16,10 @@
 
 using namespace mdk;
 
+// A replayed graph starts and ends with a few microseconds of idle GPU (2-6 us measured against the
+// same kernels launched one by one), so runs of steps replay one graph of kGraphSteps steps.
+constexpr int kGraphs = 5, kManySteps = 4, kGraphSteps = 8;
+
 struct md_ctx {
   md_forcefield ff{};
   int32_t n_boxes = 0, chain_len = 0;
@@ -38,9 +42,10 @@ struct md_ctx {
   size_t ws_bytes = 0;
   hipStream_t stream = nullptr;
   hipStream_t cap = nullptr;
-  // graphs: [energy] for the cell path; [2 * build + energy] in neighbour-list mode
-  hipGraph_t graph[4] = {nullptr, nullptr, nullptr, nullptr};
-  hipGraphExec_t exec[4] = {nullptr, nullptr, nullptr, nullptr};
+  // graphs: [energy] for the cell path; [2 * build + energy] in neighbour-list mode; [kManySteps]:
+  // kGraphSteps steps without energies (not where some steps force a list build)
+  hipGraph_t graph[kGraphs] = {};
+  hipGraphExec_t exec[kGraphs] = {};
   int integrator = MD_INT_VERLET_BERENDSEN;
   int remove_com = 0;
   std::vector<double> box_mass;   // total mass of each box (from the types at init)
@@ -664,7 +669,7 @@ bool next_step_forced(const md_ctx* c) { return nl_mode(c) && c->nl_every > 0 &&
 void advance_build_counter(md_ctx* c, bool forced) { c->since_build = forced ? 0 : c->since_build + 1; }
 
 void destroy_graphs(md_ctx* c) {
-  for (int k = 0; k < 4; ++k) {
+  for (int k = 0; k < kGraphs; ++k) {
     if (c->exec[k]) (void)hipGraphExecDestroy(c->exec[k]);
     if (c->graph[k]) (void)hipGraphDestroy(c->graph[k]);
     c->exec[k] = nullptr;
@@ -677,10 +682,14 @@ md_status capture_graphs(md_ctx* c) {
   md_status st;
   if (!c->cap && (st = hip_check(c, hipStreamCreateWithFlags(&c->cap, hipStreamNonBlocking), "capture stream")))
     return st;
-  for (int k = 0; k < (nl_mode(c) ? 4 : 2); ++k) {
+  for (int k = 0; k < kGraphs; ++k) {
+    if (k == kManySteps ? nl_mode(c) && c->nl_every > 0 : k >= 2 && !nl_mode(c)) continue;
     if ((st = hip_check(c, hipStreamBeginCapture(c->cap, hipStreamCaptureModeThreadLocal), "begin capture")))
       return st;
-    enqueue_step(c, c->cap, (k & 1) != 0, k >= 2);
+    if (k == kManySteps)
+      for (int u = 0; u < kGraphSteps; ++u) enqueue_step(c, c->cap, false, false);
+    else
+      enqueue_step(c, c->cap, (k & 1) != 0, k >= 2);
     hipError_t le = hipGetLastError();
     hipError_t e = hipStreamEndCapture(c->cap, &c->graph[k]);
     if ((st = hip_check(c, le, "launch during capture"))) return st;
@@ -962,6 +971,12 @@ md_status md_step(md_ctx* c, int32_t n_steps) {
   if (n_steps == 0) return MD_OK;
   md_status st;
   for (int32_t k = 0; k < n_steps; ++k) {
+    if (c->use_graph && c->exec[kManySteps] && n_steps - 1 - k >= kGraphSteps) {   // (never a forced build here)
+      if ((st = hip_check(c, hipGraphLaunch(c->exec[kManySteps], c->stream), "graph launch"))) return st;
+      for (int u = 0; u < kGraphSteps; ++u) advance_build_counter(c, false);
+      k += kGraphSteps - 1;
+      continue;
+    }
     const bool last = k == n_steps - 1;
     const bool forced = next_step_forced(c);
     if (c->use_graph) {
