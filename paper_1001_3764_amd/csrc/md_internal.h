@@ -243,7 +243,7 @@ void launch_bonded(const Views& v, const FFDev& ff, bool fp32, BondedMode mode, 
 void launch_reduce(const Views& v, bool energy, bool update, const StepOpts& o, hipStream_t s);
 // small boxes (one work-group per box): the first kernel of a step (kick) or of a bin rebuild, and
 // the last kernel of a run of steps (reduction with the energies, launch_finalize)
-constexpr int64_t kSmallAtoms = 4096;      // largest box that takes them
+constexpr int64_t kSmallAtoms = 3072;       // largest box that takes them (measured: at the kernels)
 constexpr int64_t kSmallLds = 96 << 10;     // and its LDS
 int64_t small_lds_bytes(int64_t n_atoms, int64_t n_cells);
 void launch_small_begin(const Views& v, bool kick, const StepOpts& o, const FFDev& ff, bool fp32, int64_t max_atoms,

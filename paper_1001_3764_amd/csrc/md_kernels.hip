@@ -911,16 +911,20 @@ __global__ void k_clear_pending(double* thermo, int n_boxes, int lf) {
 // binning, and the reduction of a step is done by the next step's first kernel: a step is this
 // kernel, the LJ force and the bonded kernel (three launches for eight).  Same arithmetic and same
 // orders as the kernels above, so the results are theirs bit for bit.  One CU moves a box's ~200 B
-// per atom and ranks its cells, so it pays only up to a few thousand atoms: per step, mixed, R = 2,
-// 36.7 against 40.4 us at 3,000 atoms (FP64, R = 1: 44 against 55 us at 1,800), even at 4,200 and
-// 47 against 42 us at 6,000; the line is at 4,096.
+// per atom and ranks its cells, so it pays only in the smallest boxes.  us per step in graphs of
+// eight, this path against the separate kernels: FP64 at 1,800 atoms 40.8 and 48.1, at 3,000 44.9
+// and 46.6; mixed (R = 2) 35.3 and 39.7, 40.0 and 41.3.  With four atoms per thread above 3,072 it
+// lost: FP64 at 3,600 atoms 45.6 and 44.3, at 3,900 52.6 and 47.9; mixed 43.2 and 42.4, 42.1 and
+// 41.0.  So the line is at three per thread.  In batches of 3,000-atom boxes mixed gains at every
+// count (64 boxes: 123 and 130); FP64 gains at 64 (268 and 274) but loses 1.5-2% at 4 to 16
+// boxes (16: 95.1 and 93.7).
 //   k_small_begin  the pending reduction (thermo slot kThPending), update, drift, wrap, cell counts in
 //                  LDS, scan, cell lists in LDS, ranks, ordered lists and payload
 //   k_small_end    after the last step of a call: the reduction with the energies, what is pending
 //                  applied to the velocities
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallBits = 12;   // an entry: place along x (32 bits), cell (20), atom of the box (12)
-static_assert(kSmallAtoms <= 1 << kSmallBits && kSmallLds / 4 < 1 << (32 - kSmallBits), "entry fields");
+static_assert(kSmallAtoms <= 3 * kSmallThreads && kSmallAtoms <= 1 << kSmallBits && kSmallLds / 4 < 1 << (32 - kSmallBits), "entry fields");
 
 template <typename F, typename PayT, bool GROUP, bool KICK, bool COM, int PER>
 __global__ __launch_bounds__(kSmallThreads) void k_small_begin(Views v, const F* __restrict__ f, double dt, double kdt,
@@ -1250,8 +1254,8 @@ void launch_small_k(const Views& v, const StepOpts& o, const FFDev& ff, int64_t 
     if (com) MDK_SMALL(true, 2);
     else MDK_SMALL(false, 2);
   } else {
-    if (com) MDK_SMALL(true, 4);
-    else MDK_SMALL(false, 4);
+    if (com) MDK_SMALL(true, 3);
+    else MDK_SMALL(false, 3);
   }
 #undef MDK_SMALL
 }

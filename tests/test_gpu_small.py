@@ -1,4 +1,4 @@
-"""Small boxes (at most 4,096 atoms): one work-group per box bins them and reduces the previous step.  The same
+"""Small boxes (at most 3,072 atoms): one work-group per box bins them and reduces the previous step.  The same
 bits as the separate kernels, which md_step_timed launches for every box."""
 import numpy as np
 import pytest
@@ -10,11 +10,11 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("chains,precision,kernel,integrator,com,graph", [
     (128, "mixed", 2, "verlet", False, True),       # 2,048 atoms: two per thread
-    (129, "fp64", 2, "leapfrog", True, False),      # four per thread
+    (129, "fp64", 2, "leapfrog", True, False),      # three per thread
     (129, "mixed", 6, "verlet", True, True),
-    (256, "fp64", 1, "verlet", True, True),         # 4,096 atoms: the largest
-    (256, "mixed", 1, "leapfrog", False, True),
-    (257, "mixed", 2, "verlet", False, False),      # past it: the separate kernels on both sides
+    (192, "fp64", 1, "verlet", True, True),         # 3,072 atoms: the largest
+    (192, "mixed", 1, "leapfrog", False, True),
+    (193, "mixed", 2, "verlet", False, False),      # past it: the separate kernels on both sides
 ])
 def test_same_bits_as_the_separate_kernels(ff, chains, precision, kernel, integrator, com, graph):
     """Runs of 1, 12 and 20 steps (one step, one graph of several steps and singles, two of them)."""
@@ -45,7 +45,7 @@ def test_batch_of_small_boxes(ff):
     """Three small boxes in one context, each equal to the box alone, bit for bit."""
     from paper_1001_3764_amd.md import MDSystem
     melts = [make_melt(c, chain_len=16, density=0.80, T=400.0, seed_melt=60 + c, seed_vel=3, jitter=0.05)
-             for c in (90, 256, 131)]
+             for c in (90, 192, 131)]
     cat = [np.concatenate(a, axis=-1) for a in zip(*[(m.pos, m.vel, m.types) for m in melts])]
     kw = dict(chain_len=16, precision="mixed", cell_div=1, lj_kernel=1)
     s = MDSystem(ff, [m.n_chains for m in melts], np.stack([m.box for m in melts]), [300.0, 0.0, 420.0], *cat,
