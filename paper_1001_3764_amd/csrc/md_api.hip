@@ -364,6 +364,7 @@ size_t carve(const Plan& p, char* base, Views* v) {
   t.n_boxes = p.n_boxes;
   t.n_atom_blocks = p.n_atom_blocks;
   t.n_lj_blocks = p.n_lj_blocks;
+  t.box_pay = p.prec == MD_PREC_MIXED && !p.group && !p.half && !p.nl_cap;
   for (const GroupDev& g : p.groups) t.lj_wave_mask |= g.waves == kSplit ? 2 : 1;
   t.boxes = (const BoxDev*)take(sizeof(BoxDev) * p.n_boxes);
   t.blk_box = (const int32_t*)take(4 * (size_t)p.n_atom_blocks);
@@ -564,13 +565,14 @@ md_status configure(md_ctx* c, const md_config* cfg, int R, int kernel) {
           o[0] = code % W - R;
           o[1] = code / W % W - R;
           o[2] = code / (W * W) - R;
-        } else if (code != kSentinelCode) {
+        } else if (code != kSentinelCode && code != kBoxCode) {
           continue;
         }
         const size_t at = ((size_t)b * kShiftSlots + code) * 3;
         for (int d = 0; d < 3; ++d) {
-          qi[at + d] = o[d] * p.boxes[b].edge_q[d];
-          qd[at + d] = o[d] * p.boxes[b].edge[d];
+          const BoxDev& B = p.boxes[b];
+          qi[at + d] = code == kBoxCode ? fix_coord(B.L[d]) : o[d] * B.edge_q[d];
+          qd[at + d] = code == kBoxCode ? B.L[d] : o[d] * B.edge[d];
         }
       }
     const bool mixed = p.prec == MD_PREC_MIXED;

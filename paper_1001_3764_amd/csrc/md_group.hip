@@ -33,7 +33,6 @@ template <bool FP64>
 constexpr int kGroupEu = FP64 ? 5 : 4;   // waves per SIMD the registers are held to
 constexpr int kChunkWindows = 64;    // 64-candidate windows whose run starts are marked at a time
 constexpr double kGap = 1e-3;        // A added to every reach and to the filter: their FP32 rounding
-constexpr float kFix2F = 1.125899906842624e15f;   // 2^50
 
 struct Cand32 {      // mixed: offsets from the group's first atom in 2^-25 A, biased by 2^31
   uint32_t x, y, z;
@@ -101,12 +100,12 @@ __device__ __forceinline__ float ext(float x) {
 
 // x + x rotated by 4 within 16-lane rows
 __device__ __forceinline__ float add_ror4(float x) {
-  return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x124, 0xf, 0xf, false));
+  return x + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x124, 0xf, 0xf, true));
 }
 __device__ __forceinline__ double add_ror4(double x) {
   const unsigned long long b = (unsigned long long)__double_as_longlong(x);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, 0x124, 0xf, 0xf, false);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), 0x124, 0xf, 0xf, false);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)b, 0x124, 0xf, 0xf, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(b >> 32), 0x124, 0xf, 0xf, true);
   return x + __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 // Sum over the 16 lanes that share lane & 3.
@@ -116,13 +115,6 @@ __device__ __forceinline__ double home_sum(double x) {
 
 __device__ inline float lane_value_f(float x, int k) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), k));
-}
-
-// LDS is written and read by one wavefront, which executes its LDS accesses in order: only the
-// compiler has to keep them so.
-__device__ __forceinline__ void lds_order() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
 }
 
 // NW wavefronts work on one group, each on every NW-th batch of its candidates (NW > 1: boxes with
@@ -271,21 +263,23 @@ void k_lj_group(Views v, FFDev ff, LjPair<float> cf, LjPair<double> cd) {
                 }
               }
             } else {
-              bool rare[NH];
-              bool any = false;
+              uint64_t rare[NH];   // (lane masks: combined by the scalar unit)
+              uint64_t any = 0;
 #pragma unroll
               for (int h = 0; h < NH; ++h) {
-                const bool keep = (uint32_t)(jt - win[h].x) > (uint32_t)win[h].y;
+                const uint64_t keep = __builtin_amdgcn_ballot_w64((uint32_t)(jt - win[h].x) > (uint32_t)win[h].y);
                 const int tt = UNI ? 0 : tag_type(pay_tag(hq[h])) * 2 + tag_type(jt);
                 const float dx = (float)(int)(hq[h].x - q.x), dy = (float)(int)(hq[h].y - q.y),
                             dz = (float)(int)(hq[h].z - q.z);
                 const float r2s = r2_fix(dx, dy, dz);
-                const bool in = keep && r2s < cf.band_hi;
-                // a close contact, or a pair whose side of the cutoff FP32 cannot tell
-                rare[h] = in && (uint32_t)(__float_as_int(r2s) - __float_as_int(cf.close)) >=
-                                    (uint32_t)(__float_as_int(cf.band_lo) - __float_as_int(cf.close));
-                any = any || rare[h];
-                const bool hit = in && !rare[h];
+                const uint64_t in = keep & __builtin_amdgcn_ballot_w64(r2s < cf.band_hi);
+                // neither a close contact nor a pair whose side of the cutoff FP32 cannot tell
+                const uint64_t plain =
+                    __builtin_amdgcn_ballot_w64((uint32_t)(__float_as_int(r2s) - __float_as_int(cf.close)) <
+                                                (uint32_t)(__float_as_int(cf.band_lo) - __float_as_int(cf.close)));
+                rare[h] = in & ~plain;
+                any |= rare[h];
+                const bool hit = __builtin_amdgcn_inverse_ballot_w64(in & plain);
                 const float r2i = rcp_f(r2s) * kFix2F;
                 const float r4 = r2i * r2i, r6 = r4 * r2i;
                 const float t = UNI ? __builtin_fmaf(cf.f12_fold, r6, -1.0f)
@@ -301,14 +295,14 @@ void k_lj_group(Views v, FFDev ff, LjPair<float> cf, LjPair<double> cd) {
                   w += (double)(UNI ? r6 * t * cf.f6[0] : r6 * t);
                 }
               }
-              if (__builtin_amdgcn_ballot_w64(any) != 0) {
+              if (any != 0) {
                 // from the FP64 positions; summed over each home's lanes into its FP64 slot
 #pragma unroll
                 for (int h = 0; h < NH; ++h) {
                   const int32_t ht = pay_tag(hq[h]);
                   const int tt = UNI ? 0 : tag_type(ht) * 2 + tag_type(jt);
                   double fx = 0.0, fy = 0.0, fz = 0.0;
-                  if (rare[h]) {
+                  if (__builtin_amdgcn_inverse_ballot_w64(rare[h])) {
                     double d[3], q2;
                     if (inside_cutoff_f64(v.pos, v.N, B, tag_index(ht), tag_index(jt), ff.rc2, d, q2))
                       add_close_pair<ENERGY>(d, q2, pick(cd.f12, tt), pick(cd.f6, tt), pick(cd.e12, tt),

@@ -20,9 +20,9 @@ constexpr int kHalo = 3;          // a dihedral reaches 3 atoms beyond its first
 constexpr double kAccUnit = 4.184e-4;
 constexpr double kRgas = 1.987204259e-3;
 
-// Mixed-precision payload: coordinates relative to the cell centre as int32 fixed
-// point in units of 2^-25 A, so differences (and cell shifts) are exact integers and
-// are rounded once when converted to FP32.  Range: |value| < 64 A.
+// Mixed-precision payload: coordinates as int32 fixed point in units of 2^-25 A, relative to the
+// cell centre (|value| < 64 A) or in the box modulo 128 A, so differences (and shifts) are exact
+// integers and are rounded once when converted to FP32.
 constexpr int kFixBits = 25;
 constexpr double kFix = 33554432.0;               // 2^25
 constexpr float kInvFixF = 2.98023223876953125e-8f;   // 2^-25
@@ -144,6 +144,7 @@ struct Views {
   int64_t N, C;            // atoms, cells (all boxes)
   int32_t n_boxes, R;
   int32_t n_atom_blocks, n_lj_blocks;
+  int32_t box_pay;         // 1: the payload is in box coordinates and index order (mixed cell kernels)
   int32_t lj_wave_mask;    // group kernel: bit 0 / 1: some box has one / kSplit waves per group
   const BoxDev* boxes;
   const GroupDev* groups;      // [n_boxes] (group kernel; else null)
@@ -161,7 +162,8 @@ struct Views {
   int32_t* cell_atoms; // [N] ordered cell lists
   int32_t* scell;      // [N] cell of each sorted slot
   void* payload;       // [N] int4 fixed point (mixed) / double4 (fp64): xyz + tag, cell-centre-relative, or
-                       // for the group kernel box coordinates (modulo 2^32 in fixed point) sorted by x in a cell
+                       // (cell path but the half shell) box coordinates, modulo 2^32 in fixed point; for the
+                       // group kernel sorted by x in a cell
   void* f_lj;          // [3N] LJ force, prec
   void* f_tot;         // [3N] total force, prec
   unsigned long long* f_acc;   // [3N] half-shell LJ force, int64 fixed point (2^-32 kcal/mol/A); zero between uses
@@ -296,6 +298,7 @@ constexpr int kTileMaxR = 2;      // stencil radii the cell-tile kernel supports
 // every home atom, so they never count and need no bounds test.
 constexpr int kShiftSlots = 128;
 constexpr int kSentinelCode = kShiftSlots - 1;
+constexpr int kBoxCode = kShiftSlots - 2;   // slot of the box's edges (mixed: modulo 2^32)
 constexpr uint32_t kSentinelEntry = (uint32_t)kSentinelCode;
 
 }  // namespace mdk

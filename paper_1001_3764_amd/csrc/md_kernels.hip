@@ -362,6 +362,10 @@ __global__ __launch_bounds__(kAtomBlock) void k_rank_payload(Views v, const int3
   const int kz = cell_coord(z, B.cinv[2], B.M[2]);
   const double rx = rel_coord(x, kx, B.edge[0]), ry = rel_coord(y, ky, B.edge[1]), rz = rel_coord(z, kz, B.edge[2]);
   const int32_t tag = atom_tag(i, ty, kx);
+  if (v.box_pay) {
+    group_payload<PayT>(static_cast<PayT*>(v.payload), dst, x, y, z, tag);
+    return;
+  }
   store_payload<PayT>(static_cast<PayT*>(v.payload), dst, rx, ry, rz, tag);
   if (v.nl_cap) {   // neighbour-list mode: where the list build saw the atom; the current payload
     store_payload<PayT>(static_cast<PayT*>(v.pay_cur), dst, rx, ry, rz, tag);   // is the build's
@@ -1073,8 +1077,8 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_begin(Views v, const F*
     v.scell[dst] = B.cell_off + (int32_t)c;
     const int kx = cell_coord(px, B.cinv[0], B.M[0]);
     const int32_t tag = atom_tag(i, type, kx);
-    if constexpr (GROUP) {
-      group_payload<PayT>(static_cast<PayT*>(v.payload), kdst, px, py, pz, tag);
+    if (GROUP || v.box_pay) {
+      group_payload<PayT>(static_cast<PayT*>(v.payload), GROUP ? kdst : dst, px, py, pz, tag);
     } else {
       const int ky = cell_coord(py, B.cinv[1], B.M[1]), kz = cell_coord(pz, B.cinv[2], B.M[2]);
       store_payload<PayT>(static_cast<PayT*>(v.payload), dst, rel_coord(px, kx, B.edge[0]),

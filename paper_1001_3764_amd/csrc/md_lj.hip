@@ -13,10 +13,10 @@
 // (2^-25 A), so x_i - x_j is an exact integer rounded once to FP32; FP64 uses doubles.
 //
 // Kernels (the rest of the cell path is in md_group.hip):
-//   k_lj_tile        one wavefront per home cell: the cell's atoms are wave-uniform (KMAX
-//                    at a time) and the stencil's atoms, listed flat in LDS and filtered
-//                    by the box bounding the homes, stream across the lanes 64 at a time;
-//                    with LIST the candidates are the cell's neighbour list instead;
+//   k_lj_cell        mixed precision, one wavefront per home cell: the cell's atoms are
+//                    wave-uniform (KMAX at a time) and the stencil's atoms, filtered by the
+//                    box bounding the homes, stream across the lanes 64 at a time;
+//   k_lj_tile        the same layout over the cell's neighbour list (nl mode);
 //   k_lj_half        the same layout over half the stencil, each pair once, both forces
 //                    added to int64 fixed-point accumulators (opt-in);
 //   k_nl_build,      neighbour-list builds (Sections 3.1-3.2), per atom and per cell, and
@@ -32,8 +32,6 @@ namespace {
 // array of candidates in LDS (sorted-array index << 7 | stencil offset code), and streams
 // that list 64 lanes at a time against up to KMAX home atoms held wave-uniform.
 constexpr int kListCap = 1024;   // candidates a wave lists at a time
-constexpr int kCompacted = -2;   // `resident` when the list holds a home group's filtered candidates
-constexpr int kFilterSteps = 4;  // candidate steps the filter loads at once
 static_assert(kListCap / 64 <= 32, "the list build keeps one bit per 64-candidate step");
 constexpr int kMaxStencil = (2 * kTileMaxR + 1) * (2 * kTileMaxR + 1) * (2 * kTileMaxR + 1);
 static_assert(kMaxStencil <= 128, "stencil code must fit 7 bits");
@@ -101,27 +99,20 @@ __device__ __forceinline__ int fill_list(const Views& v, const BoxDev& B, int lc
 }
 
 // The candidate list of home cell lc, entries [c0, c0 + kListCap), into list[]; returns its
-// full length.  Cell path: the whole stencil, listed here.  Neighbour-list mode with cell
-// lists (LIST): the cell's own list, the candidates within rc + skin of any of its atoms at
+// full length: the cell's own list, the candidates within rc + skin of any of its atoms at
 // the last build (k_nl_build_tile), copied from HBM; a cell whose list outgrew its capacity
 // streams its whole stencil instead (the bins of the build: every atom has moved less than
 // half the skin since, and the stencil covers rc + skin, so every pair within rc is in it).
 // The chunk is padded with the sentinel entry from its end up to and including the next
 // multiple of 64 (list holds kListCap + 65 entries).
-template <bool LIST>
 __device__ __forceinline__ int load_list(const Views& v, const BoxDev& B, int lc, int c0, uint32_t* list) {
-  int n;
-  if constexpr (!LIST) {
+  int n = v.nl_count[B.cell_off + lc];
+  if (n > v.nl_cap) {
     n = fill_list(v, B, lc, c0, list);
   } else {
-    n = v.nl_count[B.cell_off + lc];
-    if (n > v.nl_cap) {
-      n = fill_list(v, B, lc, c0, list);
-    } else {
-      const uint32_t* __restrict__ src = v.nl_list + B.nl_off + (int64_t)lc * v.nl_cap;
-      const int m = min(kListCap, n - c0);
-      for (int t = lane(); t < m; t += 64) list[t] = src[c0 + t];
-    }
+    const uint32_t* __restrict__ src = v.nl_list + B.nl_off + (int64_t)lc * v.nl_cap;
+    const int m = min(kListCap, n - c0);
+    for (int t = lane(); t < m; t += 64) list[t] = src[c0 + t];
   }
   const int cn = min(kListCap, n - c0);
   if (lane() <= ((cn + 63) & ~63) - cn) list[cn + lane()] = kSentinelEntry;
@@ -142,12 +133,11 @@ struct BandEnergy {
 // steps or pairs than the slots hold (not expected in a melt) every candidate of the group is
 // walked again instead, from the full list (total entries).  LDS executes a wave's accesses in
 // order and only this wave wrote its slots, so no barrier is needed.  `resident` is the chunk
-// the list holds, or kCompacted when it holds the group's ncand filtered candidates (the
-// positions the steps were recorded at); it is updated.
-template <bool ENERGY, bool UNI, bool LIST, int SHIFT>
+// the list holds; it is updated.
+template <bool ENERGY, bool UNI, int SHIFT>
 __device__ __forceinline__ BandEnergy settle_group(const Views& v, int chain_len, int excl, double rc2,
                                                    const LjPair<float>& cf, const LjPair<double>& cd,
-                                                   const BoxDev& B, Band bd, int lc, int total, int ncand,
+                                                   const BoxDev& B, Band bd, int lc, int total,
                                                    uint32_t* list, int& resident, const Shift<int>* shifts,
                                                    const int* steps, int32_t* bq, const int4* __restrict__ pay,
                                                    int hs, int g0, int kc, int nsteps) {
@@ -205,13 +195,13 @@ __device__ __forceinline__ BandEnergy settle_group(const Views& v, int chain_len
     for (int s = 0; s < nsteps; ++s) {
       const int fs = steps[s];
       const int c0 = fs - fs % kListCap;
-      if (resident != kCompacted && c0 != resident) {
-        load_list<LIST>(v, B, lc, c0, list);
+      if (c0 != resident) {
+        load_list(v, B, lc, c0, list);
         resident = c0;
       }
       int jx, jy, jz;
       int32_t jt;
-      const bool act = candidate(fs - c0 + ln, min(kListCap, ncand - c0), jx, jy, jz, jt);
+      const bool act = candidate(fs - c0 + ln, min(kListCap, total - c0), jx, jy, jz, jt);
       for (int k = 0; k < kc; ++k) {
         const int4 hq = pay[hs + g0 + k];
         int32_t hlo;
@@ -256,7 +246,7 @@ __device__ __forceinline__ BandEnergy settle_group(const Views& v, int chain_len
       double cx = 0.0, cy = 0.0, cz = 0.0;
       for (int c0 = 0; c0 < total; c0 += kListCap) {
         if (c0 != resident) {
-          load_list<LIST>(v, B, lc, c0, list);
+          load_list(v, B, lc, c0, list);
           resident = c0;
         }
         const int cn = min(kListCap, total - c0);
@@ -324,9 +314,8 @@ __device__ __forceinline__ void sum_homes(int ln, P (&ax)[KMAX], P (&ay)[KMAX], 
 // Occupancy targets (measured): the mixed form with 8 homes is held to 6 waves per SIMD (80
 // VGPRs; it uses 73, with no vector spills), 4 homes to 8 and 16 homes to 4; the FP64 form
 // (K = 4) fits 8.
-// LIST: neighbour-list mode with per-cell lists (the homes and the sorted order are those of
-// the last build, the payload the one refreshed since).
-template <bool FP64, bool ENERGY, bool UNI, int KMAX, bool BRANCHLESS, bool LIST = false>
+// (the homes and the sorted order are those of the last build, the payload the one refreshed since)
+template <bool FP64, bool ENERGY, bool UNI, int KMAX>
 __global__ __launch_bounds__(64 * kTileWaves)
 __attribute__((amdgpu_waves_per_eu(FP64 ? 8 : (KMAX >= 16 ? 4 : (KMAX <= 4 ? 8 : 6)))))
 void k_lj_tile(Views v, FFDev ff, LjPair<float> cf, LjPair<double> cd) {
@@ -358,7 +347,7 @@ void k_lj_tile(Views v, FFDev ff, LjPair<float> cf, LjPair<double> cd) {
   // stencil offsets in the payload's units (the same for every wave of the block)
   load_shifts(v, b, shifts);
   int total = 0, resident = 0;
-  if (wact) total = __builtin_amdgcn_readfirstlane(load_list<LIST>(v, B, lc, 0, list[wave]));
+  if (wact) total = __builtin_amdgcn_readfirstlane(load_list(v, B, lc, 0, list[wave]));
   __syncthreads();
 
   double e = 0.0, es = 0.0, w = 0.0;
@@ -386,67 +375,7 @@ void k_lj_tile(Views v, FFDev ff, LjPair<float> cf, LjPair<double> cd) {
         span_l = (uint32_t)(min(i + ff.excl, c0 + ff.chain_len - 1) - lo_l);
         ht_l = tag_type(pay_tag(qh));
       }
-      // Cell path with a one-chunk list: keep only the candidates within the cutoff of the
-      // box bounding the group's homes (about half of the stencil's atoms in a melt),
-      // compacted in place.  Per axis |x - clamp(x, lo, hi)| <= |x - x_home| for every home
-      // in the box, and each rounding is monotone, so the filter's r^2 (the pair test's
-      // own operation order in the mixed form) never exceeds a pair's: no counted pair is
-      // dropped.  Each batch's reads precede its writes and land at or above them.
-      int ncand = total;    // list entries the step loop walks
-      if (!LIST && total <= kListCap) {
-        if (resident != 0) {
-          load_list<LIST>(v, B, lc, 0, list[wave]);
-          resident = 0;
-        }
-        // the box bounding the homes, reduced over the first KMAX lanes (in vector registers:
-        // the clamp reads both bounds of an axis)
-        const bool hv = ln < kc;
-        Q lox = first_lanes_min<KMAX>(hv ? qh.x : box_top<Q>()), hix = first_lanes_max<KMAX>(hv ? qh.x : -box_top<Q>());
-        Q loy = first_lanes_min<KMAX>(hv ? qh.y : box_top<Q>()), hiy = first_lanes_max<KMAX>(hv ? qh.y : -box_top<Q>());
-        Q loz = first_lanes_min<KMAX>(hv ? qh.z : box_top<Q>()), hiz = first_lanes_max<KMAX>(hv ? qh.z : -box_top<Q>());
-        const double rc2_keep = ff.rc2 * (1.0 + 1e-12);
-        int m = 0;
-        constexpr int kFilter = FP64 ? 2 : kFilterSteps;
-        // NU steps from position t0 (all below the padded end, whose entries past total are the
-        // sentinel, which never passes); a batch reads all its entries before it writes any
-        auto batch = [&](int t0, auto nu) {
-          constexpr int NU = decltype(nu)::value;
-          uint32_t ent[NU];
-          Q jx[NU], jy[NU], jz[NU];
-#pragma unroll
-          for (int u = 0; u < NU; ++u) ent[u] = list[wave][t0 + 64 * u + ln];
-#pragma unroll
-          for (int u = 0; u < NU; ++u) {
-            const PayT q = pay[ent[u] >> 7];
-            const Shift<Q> sh = shifts[ent[u] & 127];
-            jx[u] = q.x + sh.x;
-            jy[u] = q.y + sh.y;
-            jz[u] = q.z + sh.z;
-          }
-#pragma unroll
-          for (int u = 0; u < NU; ++u) {
-            const Q dx = jx[u] - clamp_box(jx[u], lox, hix), dy = jy[u] - clamp_box(jy[u], loy, hiy),
-                    dz = jz[u] - clamp_box(jz[u], loz, hiz);
-            bool pass;
-            if constexpr (FP64)
-              pass = dx * dx + dy * dy + dz * dz < rc2_keep;
-            else
-              pass = r2_fix((float)dx, (float)dy, (float)dz) < bd.hi;
-            const uint64_t bm = __builtin_amdgcn_ballot_w64(pass);
-            if (pass) list[wave][m + lanes_below(bm)] = ent[u];
-            m += __popcll(bm);
-          }
-        };
-        // whole batches of kFilter steps with their loads in flight together, then single steps
-        const int tp = (total + 63) & ~63;
-        int t0 = 0;
-        for (; t0 + 64 * kFilter <= tp; t0 += 64 * kFilter) batch(t0, std::integral_constant<int, kFilter>());
-        for (; t0 < tp; t0 += 64) batch(t0, std::integral_constant<int, 1>());
-        if (ln < ((m + 63) & ~63) - m) list[wave][m + ln] = kSentinelEntry;   // pad to whole steps
-        ncand = m;
-        resident = kCompacted;
-      }
-      // the homes broadcast to wave-uniform values (after the filter, which needs only their box)
+      // the homes broadcast to wave-uniform values
       Q hx[KMAX], hy[KMAX], hz[KMAX];
       int32_t lo[KMAX], hti[KMAX];
       uint32_t span[KMAX];
@@ -463,12 +392,12 @@ void k_lj_tile(Views v, FFDev ff, LjPair<float> cf, LjPair<double> cd) {
       }
       int nsteps = 0;       // candidate steps with a band pair or a close contact (wave-uniform)
       int32_t bmax = 0;     // bits of the largest r2s counted since the last band check
-      for (int c0 = 0; c0 < ncand; c0 += kListCap) {
-        if (resident != kCompacted && c0 != resident) {
-          load_list<LIST>(v, B, lc, c0, list[wave]);
+      for (int c0 = 0; c0 < total; c0 += kListCap) {
+        if (c0 != resident) {
+          load_list(v, B, lc, c0, list[wave]);
           resident = c0;
         }
-        const int cn = min(kListCap, ncand - c0);
+        const int cn = min(kListCap, total - c0);
         for (int t0 = 0; t0 < cn; t0 += 64) {
           // the list is padded to whole steps with the sentinel, which lies beyond the cutoff
           const uint32_t ent = list[wave][t0 + ln];
@@ -493,7 +422,7 @@ void k_lj_tile(Views v, FFDev ff, LjPair<float> cf, LjPair<double> cd) {
                                  pick(cd.f6, tt), pick(cd.e12, tt), pick(cd.e6, tt), pick(cd.ecut, tt), ax[k],
                                  ay[k], az[k], e, es, w);
               else
-                pair_fix<ENERGY, BRANCHLESS, UNI>(hx[k] - jx, hy[k] - jy, hz[k] - jz, keep, bd,
+                pair_fix<ENERGY, UNI>(hx[k] - jx, hy[k] - jy, hz[k] - jz, keep, bd,
                                                   UNI ? f12_fold : pick(cf.f12, tt), pick(cf.f6, tt),
                                                   pick(cf.e12, tt), pick(cf.e6, tt), pick(cf.ecut, tt), ax[k],
                                                   ay[k], az[k], e, es, w, bmax, near);
@@ -556,8 +485,8 @@ void k_lj_tile(Views v, FFDev ff, LjPair<float> cf, LjPair<double> cd) {
       }
       if constexpr (!FP64) {
         if (nsteps > 0) {
-          const BandEnergy be = settle_group<ENERGY, UNI, LIST, 6 - LV>(v, ff.chain_len, ff.excl, ff.rc2, cf, cd, B, bd,
-                                                                       lc, total, ncand, list[wave], resident, shifts,
+          const BandEnergy be = settle_group<ENERGY, UNI, 6 - LV>(v, ff.chain_len, ff.excl, ff.rc2, cf, cd, B, bd,
+                                                                       lc, total, list[wave], resident, shifts,
                                                                        bsteps[wave], bq[wave], pay, hs, g0, kc, nsteps);
           if (ENERGY) {
             e += be.e;
@@ -569,6 +498,331 @@ void k_lj_tile(Views v, FFDev ff, LjPair<float> cf, LjPair<double> cd) {
     }
   }
   if (ENERGY) block_energy<kTileWaves>(e, es, w, red, v.part_lj + (int64_t)blk * 3);
+}
+
+// ---------------------------------------------------------------------------------
+// Cell path, mixed precision (MD_LJ_CELLTILE, MD_LJ_CELLTILE_NB): one wave per home cell.  The cells
+// of a stencil row are consecutive in the sorted order, so the (2R + 1)^3 stencil is (2R + 1)^2 runs,
+// or two where the box's edge cuts a row; lane r < 32 finds the part of row r inside the box and lane
+// 32 + r the part across the edge.  The wave streams the runs 64 candidates at a time (each lane's
+// run from a bit mask of run starts); a candidate nearer than rc to the box bounding up to KMAX homes
+// goes, in the frame of the cell's first atom, to a list in LDS, which is then taken 64 at a time
+// against the homes, held wave-uniform.  The payload is in box coordinates (modulo 128 A).
+//
+// Bound: VALU issue (1,460 instructions per cell of 5.2 atoms at R = 2, about half of them pairs: 24
+// each for 27.8 steps of 64; the rest set-up, 10 windows of 35 and the sums).  The form before listed
+// every candidate's index in LDS and gathered the payload twice (1,605 instructions).  LJ pass, event
+// timing: 300,000 atoms 159 -> 152 us; a step of 24 boxes of 453,600 atoms 272 -> 262 us, of 3,000 atoms
+// 40.0 -> 38.7 us, of 3,000,000 atoms 1,630 -> 1,618 us.  Force error against FP64 as before (rms 5.06e-7
+// over 24 melts).  Measured as well: the homes by scalar loads, no change.
+// fixed-point coordinates modulo 2^32
+__device__ inline int fix_add(int a, int b) { return (int)((uint32_t)a + (uint32_t)b); }
+__device__ inline int fix_sub(int a, int b) { return (int)((uint32_t)a - (uint32_t)b); }
+
+constexpr int kRunWindows = 64;   // 64-candidate windows whose run starts are marked at a time
+constexpr int kRunBatch = 2;      // windows whose loads are in flight together
+constexpr double kFilterGap = 1e-3;   // A added to the filter's reach: the rounding of its FP32 distances
+constexpr int kStage = 288;           // candidates held in LDS (16 B each): 24 waves per CU with the rest (at 304, 21)
+
+template <bool ENERGY, bool UNI, int KMAX, bool BRANCHLESS>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(KMAX >= 16 ? 4 : 6)))
+void k_lj_cell(Views v, FFDev ff, LjPair<float> cf, LjPair<double> cd) {
+  constexpr int LV = KMAX == 16 ? 4 : (KMAX == 8 ? 3 : 2);   // log2(KMAX)
+  static_assert((1 << LV) == KMAX, "KMAX must be 4, 8 or 16");
+  static_assert(kTileWaves == 1, "one wave per block");
+  static_assert((2 * kTileMaxR + 1) * (2 * kTileMaxR + 1) <= 32, "a row per lane of half a wave");
+  constexpr int CAP = kStage;
+  __shared__ int4 list[CAP];
+  __shared__ int4 runs[64];   // x, y, z: added to a payload coordinate; w: to a flat position, in bytes of payload
+  __shared__ unsigned long long marks[kRunWindows];
+  __shared__ double exact[KMAX][3];   // forces of the pairs evaluated in FP64
+  __shared__ dd red[1][3];
+
+  const int ln = lane();
+  // Workgroups are dealt to the 8 XCDs round-robin; give each XCD a contiguous run of
+  // home cells (a slab of the box) so its L2 holds one neighbourhood of the payload.
+  const int per_xcd = (int)gridDim.x / kXcds;
+  const int blk = ((int)blockIdx.x % kXcds) * per_xcd + (int)blockIdx.x / kXcds;
+  if (blk >= v.n_lj_blocks) return;
+  const int b = v.lj_blk_box[blk];
+  const BoxDev& B = v.boxes[b];
+  const int lc = blk - B.lj_blk_off;   // home cell within the box
+  const int32_t* __restrict__ cs = v.cell_start;
+  const int4* __restrict__ pay = static_cast<const int4*>(v.payload);
+  double e = 0.0, es = 0.0, w = 0.0;
+
+  const int hs = uni(cs[B.cell_off + lc]), hn = uni(cs[B.cell_off + lc + 1]) - hs;
+  if (hn > 0) {
+    // ---- the runs ----
+    const int R = v.R, W = 2 * R + 1;
+    const int M0 = B.M[0], M1 = B.M[1], M2 = B.M[2];
+    const Cell3 k3 = cell_coords(lc, B);
+    const int row = ln & 31;
+    const int oz = (int)(((float)row + 0.5f) * rcp_f((float)W)) - R, oy = row - (oz + R) * W - R;
+    int ny = k3.y + oy, nz = k3.z + oz;
+    const int wy = ny < 0 ? -1 : (ny >= M1 ? 1 : 0), wz = nz < 0 ? -1 : (nz >= M2 ? 1 : 0);
+    ny -= wy * M1;
+    nz -= wz * M2;
+    const int xlo = k3.x - R, xhi = k3.x + R;
+    // (M0 >= 2 R + 1: a row crosses at most one edge)
+    int a = max(xlo, 0), z = min(xhi, M0 - 1), wx = 0;
+    if (ln >= 32) {
+      wx = xlo < 0 ? -1 : (xhi >= M0 ? 1 : 0);
+      a = wx < 0 ? xlo + M0 : 0;
+      z = wx < 0 ? M0 - 1 : (wx > 0 ? xhi - M0 : -1);
+    }
+    int n = 0, start = 0;
+    if (row < W * W && a <= z) {
+      const int c = B.cell_off + M0 * (ny + M1 * nz);
+      start = cs[c + a];
+      n = cs[c + z + 1] - start;
+    }
+    const int4 q0 = pay[hs];
+    const Shift<int> edge = static_cast<const Shift<int>*>(v.shift_tab)[(int64_t)b * kShiftSlots + kBoxCode];
+    int total;
+    const int f = wave_exclusive_scan(n, total);
+    total = uni(total);
+    const uint64_t some = __builtin_amdgcn_ballot_w64(n > 0);
+    if (n > 0)
+      runs[lanes_below(some)] =
+          make_int4((int)((uint32_t)wx * (uint32_t)edge.x - (uint32_t)q0.x), (int)((uint32_t)wy * (uint32_t)edge.y - (uint32_t)q0.y),
+                    (int)((uint32_t)wz * (uint32_t)edge.z - (uint32_t)q0.z), (start - f) * 16);
+    const int mark = n > 0 ? f - 1 : -1;   // a run (but the first) marks the position before it
+    const float rc = __builtin_amdgcn_sqrtf((float)ff.rc2) + (float)kFilterGap;
+    const float rcf = rc * rc * ((float)kFix * (float)kFix);
+
+    for (int g0 = 0; g0 < hn; g0 += KMAX) {
+      const int kc = min(KMAX, hn - g0);
+      // The group's homes, one per lane (lane k < kc holds home k), each with its exclusion window
+      // (the atoms within excl bonds along its chain, in tag units).  A lane past the group repeats
+      // the last home with a window that excludes every candidate.
+      const int4 qh = pay[hs + g0 + min(ln, kc - 1)];
+      const int hxl = fix_sub(qh.x, q0.x), hyl = fix_sub(qh.y, q0.y), hzl = fix_sub(qh.z, q0.z);
+      int32_t lo_l = 0, span_l = -1;
+      if (ln < kc) {
+        const int32_t i = tag_index(pay_tag(qh));
+        const int32_t c0 = chain_first(i, ff), first = max(i - ff.excl, c0);
+        lo_l = first << 4;
+        span_l = ((min(i + ff.excl, c0 + ff.chain_len - 1) - first) << 4) | 15;
+      }
+      // the box bounding the homes (in vector registers: the clamp reads both bounds of an axis)
+      const float bxl = in_vgpr((float)first_lanes_min<KMAX>(hxl)), bxh = in_vgpr((float)first_lanes_max<KMAX>(hxl));
+      const float byl = in_vgpr((float)first_lanes_min<KMAX>(hyl)), byh = in_vgpr((float)first_lanes_max<KMAX>(hyl));
+      const float bzl = in_vgpr((float)first_lanes_min<KMAX>(hzl)), bzh = in_vgpr((float)first_lanes_max<KMAX>(hzl));
+      uint32_t hx[KMAX], hy[KMAX], hz[KMAX];   // (unsigned: the padding's differences wrap)
+      int32_t lo[KMAX], hti[KMAX];
+      uint32_t span[KMAX];
+      float ax[KMAX], ay[KMAX], az[KMAX];
+#pragma unroll
+      for (int k = 0; k < KMAX; ++k) {
+        ax[k] = ay[k] = az[k] = 0.0f;
+        hx[k] = (uint32_t)lane_value(hxl, k);
+        hy[k] = (uint32_t)lane_value(hyl, k);
+        hz[k] = (uint32_t)lane_value(hzl, k);
+        lo[k] = lane_value(lo_l, k);
+        span[k] = (uint32_t)lane_value(span_l, k);
+        hti[k] = UNI ? 0 : lane_value(tag_type(pay_tag(qh)), k);
+      }
+      bool settled = false;   // exact[] holds this group's sums
+      int m = 0;              // candidates in list[]
+      int t0 = -64 * kRunWindows, w0 = 0, nw = 0, before = 0;
+      int mlo = 0, mhi = 0;
+      bool more = true;
+      do {
+        // ---- fill the list ----
+        while (m <= CAP - 64 * kRunBatch) {
+          if (w0 >= nw) {
+            t0 += 64 * kRunWindows;
+            more = t0 < total;
+            if (!more) break;
+            marks[ln] = 0ull;
+            lds_order();
+            const int at = mark - t0;
+            if (mark >= 0 && at >= 0 && at < 64 * kRunWindows) atomicOr(&marks[at >> 6], 1ull << (at & 63));
+            lds_order();
+            const unsigned long long mk = marks[ln];
+            mlo = (int)(uint32_t)mk;
+            mhi = (int)(uint32_t)(mk >> 32);
+            before = __popcll(__builtin_amdgcn_ballot_w64(mark >= 0 && at < 0));
+            nw = (min(total - t0, 64 * kRunWindows) + 63) >> 6;
+            w0 = 0;
+          }
+          int4 q[kRunBatch], run[kRunBatch];
+          uint64_t in[kRunBatch];
+#pragma unroll
+          for (int u = 0; u < kRunBatch; ++u) {
+            // lanes past the candidates repeat the last one and are dropped below
+            const int first = t0 + 64 * (w0 + u), t = first + ln;
+            const uint32_t wl = (uint32_t)__builtin_amdgcn_readlane(mlo, w0 + u);
+            const uint32_t wh = (uint32_t)__builtin_amdgcn_readlane(mhi, w0 + u);
+            const int r = (int)__builtin_amdgcn_mbcnt_hi(wh, __builtin_amdgcn_mbcnt_lo(wl, (uint32_t)before));
+            before += __popc(wl) + __popc(wh);
+            const int left = total - first;
+            in[u] = left >= 64 ? ~0ull : (left > 0 ? (1ull << left) - 1ull : 0ull);
+            run[u] = runs[r];
+            q[u] = *reinterpret_cast<const int4*>(reinterpret_cast<const char*>(pay) +
+                                                  (uint32_t)((min(t, total - 1) << 4) + run[u].w));
+          }
+#pragma unroll
+          for (int u = 0; u < kRunBatch; ++u) {
+            asm volatile("" : "+v"(q[u].w));   // (else the tag is loaded by itself once the filter has passed)
+            const int cx = fix_add(q[u].x, run[u].x), cy = fix_add(q[u].y, run[u].y), cz = fix_add(q[u].z, run[u].z);
+            const float gx = (float)cx, gy = (float)cy, gz = (float)cz;
+            const float dx = gx - __builtin_amdgcn_fmed3f(gx, bxl, bxh);
+            const float dy = gy - __builtin_amdgcn_fmed3f(gy, byl, byh);
+            const float dz = gz - __builtin_amdgcn_fmed3f(gz, bzl, bzh);
+            const uint64_t pm = __builtin_amdgcn_ballot_w64(r2_fix(dx, dy, dz) < rcf) & in[u];
+            if (__builtin_amdgcn_inverse_ballot_w64(pm))
+              list[__builtin_amdgcn_mbcnt_hi((uint32_t)(pm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)pm, (uint32_t)m))] =
+                  make_int4(cx, cy, cz, q[u].w);
+            m += __popcll(pm);
+          }
+          w0 += kRunBatch;
+        }
+        if (!more) {   // whole steps: padded with candidates 64 A from the cell's first atom
+          const int pad = ((m + 63) & ~63) - m;
+          if (ln < pad) list[m + ln] = make_int4(INT32_MIN, INT32_MIN, INT32_MIN, 0);
+          m += pad;
+        }
+        lds_order();
+        // ---- the whole steps of the list against the homes ----
+        const int ns = m >> 6;
+#pragma unroll 1
+        for (int s = 0; s < ns; ++s) {
+          const int4 q = list[64 * s + ln];
+          const int32_t jt = pay_tag(q);
+          const bool jtype = tag_type(jt) != 0;
+          // the pair factors for a home of type 0 and of type 1
+          const float f12_0 = UNI ? cf.f12_fold : (jtype ? cf.f12[1] : cf.f12[0]);
+          const float f12_1 = UNI ? cf.f12_fold : (jtype ? cf.f12[3] : cf.f12[2]);
+          const float f6_0 = UNI ? 1.0f : (jtype ? cf.f6[1] : cf.f6[0]);
+          const float f6_1 = UNI ? 1.0f : (jtype ? cf.f6[3] : cf.f6[2]);
+          uint64_t rare = 0;   // lanes with a close contact or a pair whose side of the cutoff FP32 cannot tell
+          // the group's home count, re-read each step as an opaque scalar: the compiler then
+          // tests k < kc with a scalar compare per home instead of holding KMAX lane masks
+          int kcs = kc;
+          asm volatile("" : "+s"(kcs));
+#pragma unroll
+          for (int k = 0; k < KMAX; ++k) {
+            if (k < kcs) {
+              const uint64_t keep = __builtin_amdgcn_ballot_w64((uint32_t)(jt - lo[k]) > span[k]);
+              const float dx = (float)(int)(hx[k] - (uint32_t)q.x), dy = (float)(int)(hy[k] - (uint32_t)q.y),
+                          dz = (float)(int)(hz[k] - (uint32_t)q.z);
+              const float r2s = r2_fix(dx, dy, dz);
+              // (lane masks: and-ed by the scalar unit)
+              const uint64_t in = keep & __builtin_amdgcn_ballot_w64(r2s < cf.band_hi);
+              const uint64_t plain =
+                  __builtin_amdgcn_ballot_w64((uint32_t)(__float_as_int(r2s) - __float_as_int(cf.close)) <
+                                              (uint32_t)(__float_as_int(cf.band_lo) - __float_as_int(cf.close)));
+              const bool hit = __builtin_amdgcn_inverse_ballot_w64(in & plain);
+              rare |= in & ~plain;
+              if (BRANCHLESS || hit) {
+                const float r2i = rcp_f(r2s) * kFix2F;
+                const float r4 = r2i * r2i, r6 = r4 * r2i;
+                const float t6 = UNI ? __builtin_fmaf(f12_0, r6, -1.0f)
+                                     : __builtin_fmaf(hti[k] ? f12_1 : f12_0, r6, -(hti[k] ? f6_1 : f6_0));
+                float fs = (r4 * r4) * t6;
+                if (BRANCHLESS) fs = hit ? fs : 0.0f;
+                ax[k] = __builtin_fmaf(fs, dx, ax[k]);
+                ay[k] = __builtin_fmaf(fs, dy, ay[k]);
+                az[k] = __builtin_fmaf(fs, dz, az[k]);
+                if (ENERGY && hit) {
+                  const int tt = UNI ? 0 : hti[k] * 2 + (int)jtype;
+                  const float en = r6 * (pick(cf.e12, tt) * r6 - pick(cf.e6, tt));
+                  e += (double)en;
+                  es += (double)en - (double)pick(cf.ecut, tt);
+                  w += (double)(UNI ? r6 * t6 * cf.f6[0] : r6 * t6);
+                }
+              }
+            }
+          }
+          if (rare != 0) {
+            // those pairs from the FP64 positions, summed over the lanes in a fixed order
+            if (!settled && ln < KMAX) exact[ln][0] = exact[ln][1] = exact[ln][2] = 0.0;
+            settled = true;
+            lds_order();
+#pragma unroll 1
+            for (int k = 0; k < kc; ++k) {
+              const int4 h = pay[hs + g0 + k];
+              const int32_t i = tag_index(pay_tag(h)), c0 = chain_first(i, ff), first = max(i - ff.excl, c0);
+              const uint32_t wide = (uint32_t)(min(i + ff.excl, c0 + ff.chain_len - 1) - first);
+              const float r2s = r2_fix((float)fix_sub(fix_sub(h.x, q0.x), q.x), (float)fix_sub(fix_sub(h.y, q0.y), q.y),
+                                       (float)fix_sub(fix_sub(h.z, q0.z), q.z));
+              double px = 0.0, py = 0.0, pz = 0.0;
+              if ((uint32_t)(tag_index(jt) - first) > wide && r2s < cf.band_hi &&
+                  !(r2s >= cf.close && r2s < cf.band_lo)) {
+                double d[3], r2;
+                const int tt = UNI ? 0 : tag_type(pay_tag(h)) * 2 + (int)jtype;
+                if (inside_cutoff_f64(v.pos, v.N, B, i, tag_index(jt), ff.rc2, d, r2))
+                  add_close_pair<ENERGY>(d, r2, pick(cd.f12, tt), pick(cd.f6, tt), pick(cd.e12, tt), pick(cd.e6, tt),
+                                         pick(cd.ecut, tt), px, py, pz, e, es, w);
+              }
+              px = group_sum(px, 0);
+              py = group_sum(py, 0);
+              pz = group_sum(pz, 0);
+              if (ln == 0) {
+                exact[k][0] += px;
+                exact[k][1] += py;
+                exact[k][2] += pz;
+              }
+              lds_order();
+            }
+          }
+        }
+        if (more) {   // what is left moves to the front (LDS runs a wave's accesses in order)
+          const int rest = m & 63;
+          if (ln < rest) list[ln] = list[64 * ns + ln];
+          m = rest;
+          lds_order();
+        }
+      } while (more);
+      // ---- each home's sums over the 64 lanes in a fixed order: lanes [h * 64/KMAX, (h + 1) * 64/KMAX)
+      // then hold home h's, and the first of them stores it (sum_homes written out: the explicit
+      // exchange patterns keep the register allocation tighter) ----
+      constexpr int NV = 3 * KMAX;
+      float val[NV];
+#pragma unroll
+      for (int k = 0; k < KMAX; ++k) {
+        val[3 * k] = ax[k];
+        val[3 * k + 1] = ay[k];
+        val[3 * k + 2] = az[k];
+      }
+#pragma unroll
+      for (int lv = 0; lv < LV; ++lv) {
+#pragma unroll
+        for (int i = 0; i < (NV >> lv) / 2; ++i) {
+          const int h = (NV >> lv) / 2 + i;
+          if (lv < 2) {
+            val[i] = swap_sum(val[i], val[h], kLevel[lv]);
+          } else {
+            const bool hi = (ln & (32 >> lv)) != 0;
+            const float send = hi ? val[i] : val[h];
+            const float keep = hi ? val[h] : val[i];
+            val[i] = keep + partner(send, lv == 2 ? Xl::Ror8 : Xl::Mirror8);
+          }
+        }
+      }
+#pragma unroll
+      for (int c = 0; c < 3; ++c) val[c] = group_sum(val[c], LV);
+      const int hk = ln >> (6 - LV);
+      const int32_t i = tag_index(__shfl(pay_tag(qh), hk));   // home hk's index, from lane hk
+      if ((ln & ((64 >> LV) - 1)) == 0 && hk < kc) {
+        const double sc = (double)kInvFixF * (UNI ? cd.f6[0] : 1.0);   // fixed-point units; divided by f6 with one type pair
+        double ox = (double)val[0] * sc, oyv = (double)val[1] * sc, ozv = (double)val[2] * sc;
+        if (settled) {
+          ox += exact[hk][0];
+          oyv += exact[hk][1];
+          ozv += exact[hk][2];
+        }
+        float* fo = static_cast<float*>(v.f_lj);
+        fo[i] = (float)ox;
+        fo[v.N + i] = (float)oyv;
+        fo[2 * v.N + i] = (float)ozv;
+      }
+      lds_order();
+    }
+  }
+  if (ENERGY) block_energy<1>(e, es, w, red, v.part_lj + (int64_t)blk * 3);
 }
 
 // ---------------------------------------------------------------------------------
@@ -925,7 +1179,7 @@ __global__ __launch_bounds__(64 * kTileWaves) void k_nl_build(Views v, FFDev ff,
 // Build with per-cell lists: one wave per home cell streams its stencil as the cell tile
 // does and keeps every candidate within rc + skin of ANY atom of the cell (the union of
 // their Verlet spheres, in stencil order), so the force kernel can stream it exactly like
-// the stencil (k_lj_tile<LIST>): fewer candidates, the same coalesced loads.  Home atoms
+// the stencil (k_lj_tile): fewer candidates, the same coalesced loads.  Home atoms
 // and excluded partners stay in the list (the force kernel tests exclusions per pair).
 template <bool FP64>
 __global__ __launch_bounds__(64 * kTileWaves) void k_nl_build_tile(Views v, FFDev ff, const int32_t* __restrict__ gate) {
@@ -1060,7 +1314,7 @@ __global__ __launch_bounds__(kLjNlBlock) void k_lj_nl(Views v, FFDev ff, LjPair<
       } else {
         const int dqx = hq.x - (q.x + sh.x), dqy = hq.y - (q.y + sh.y), dqz = hq.z - (q.z + sh.z);
         bool near = false;
-        const float r2s = pair_fix<ENERGY, false, UNI>(dqx, dqy, dqz, keep, bd, UNI ? f12_fold : pick(cf.f12, tt),
+        const float r2s = pair_fix<ENERGY, UNI>(dqx, dqy, dqz, keep, bd, UNI ? f12_fold : pick(cf.f12, tt),
                                                        pick(cf.f6, tt), pick(cf.e12, tt), pick(cf.e6, tt),
                                                        pick(cf.ecut, tt), ax[u], ay[u], az[u], e, es, w, bmax, near);
         double d[3], r2;
@@ -1138,30 +1392,44 @@ __global__ __launch_bounds__(kLjNlBlock) void k_lj_nl(Views v, FFDev ff, LjPair<
   if (ENERGY) block_energy<kLjNlBlock / 64>(e, es, w, red, v.part_lj + (int64_t)blockIdx.x * 3);
 }
 
-template <bool FP64, bool ENERGY, int K, bool LIST>
-void launch_tile_k(const Views& v, const FFDev& ff, const LjPair<float>& cf, const LjPair<double>& cd,
-                   bool branchless, hipStream_t s) {
-  dim3 g((v.n_lj_blocks + kXcds - 1) / kXcds * kXcds), b(64 * kTileWaves);
-  if (ff.uniform_lj) {
-    if (branchless && !LIST)
-      hipLaunchKernelGGL((k_lj_tile<FP64, ENERGY, true, K, true>), g, b, 0, s, v, ff, cf, cd);
-    else
-      hipLaunchKernelGGL((k_lj_tile<FP64, ENERGY, true, K, false, LIST>), g, b, 0, s, v, ff, cf, cd);
-  } else {
-    hipLaunchKernelGGL((k_lj_tile<FP64, ENERGY, false, K, false, LIST>), g, b, 0, s, v, ff, cf, cd);
-  }
+template <bool FP64, bool ENERGY, int K>
+void launch_tile_k(const Views& v, const FFDev& ff, const LjPair<float>& cf, const LjPair<double>& cd, hipStream_t s) {
+  const dim3 g((v.n_lj_blocks + kXcds - 1) / kXcds * kXcds), b(64 * kTileWaves);
+  if (ff.uniform_lj) hipLaunchKernelGGL((k_lj_tile<FP64, ENERGY, true, K>), g, b, 0, s, v, ff, cf, cd);
+  else hipLaunchKernelGGL((k_lj_tile<FP64, ENERGY, false, K>), g, b, 0, s, v, ff, cf, cd);
 }
 
 // homes: home atoms per pass of a wave (4, 8 or 16; the FP64 form holds 4 in scalar registers).
-template <bool FP64, bool ENERGY, bool LIST = false>
-void launch_tile(const Views& v, const FFDev& ff, const LjPair<float>& cf, const LjPair<double>& cd,
-                 bool branchless, int homes, hipStream_t s) {
-  if (FP64 || homes == 4)
-    launch_tile_k<FP64, ENERGY, 4, LIST>(v, ff, cf, cd, branchless, s);
-  else if (homes == 16)
-    launch_tile_k<FP64, ENERGY, 16, LIST>(v, ff, cf, cd, branchless, s);
-  else
-    launch_tile_k<FP64, ENERGY, 8, LIST>(v, ff, cf, cd, branchless, s);
+template <bool FP64, bool ENERGY>
+void launch_tile(const Views& v, const FFDev& ff, const LjPair<float>& cf, const LjPair<double>& cd, int homes,
+                 hipStream_t s) {
+  if constexpr (FP64) {
+    launch_tile_k<FP64, ENERGY, 4>(v, ff, cf, cd, s);
+  } else {
+    if (homes == 4) launch_tile_k<FP64, ENERGY, 4>(v, ff, cf, cd, s);
+    else if (homes == 16) launch_tile_k<FP64, ENERGY, 16>(v, ff, cf, cd, s);
+    else launch_tile_k<FP64, ENERGY, 8>(v, ff, cf, cd, s);
+  }
+}
+
+template <bool ENERGY, int K>
+void launch_cell_k(const Views& v, const FFDev& ff, const LjPair<float>& cf, const LjPair<double>& cd,
+                   bool branchless, hipStream_t s) {
+  const dim3 g((v.n_lj_blocks + kXcds - 1) / kXcds * kXcds), b(64);
+  if (ff.uniform_lj) {
+    if (branchless) hipLaunchKernelGGL((k_lj_cell<ENERGY, true, K, true>), g, b, 0, s, v, ff, cf, cd);
+    else hipLaunchKernelGGL((k_lj_cell<ENERGY, true, K, false>), g, b, 0, s, v, ff, cf, cd);
+  } else {
+    hipLaunchKernelGGL((k_lj_cell<ENERGY, false, K, false>), g, b, 0, s, v, ff, cf, cd);
+  }
+}
+
+template <bool ENERGY>
+void launch_cell(const Views& v, const FFDev& ff, const LjPair<float>& cf, const LjPair<double>& cd, bool branchless,
+                 int homes, hipStream_t s) {
+  if (homes == 4) launch_cell_k<ENERGY, 4>(v, ff, cf, cd, branchless, s);
+  else if (homes == 16) launch_cell_k<ENERGY, 16>(v, ff, cf, cd, branchless, s);
+  else launch_cell_k<ENERGY, 8>(v, ff, cf, cd, branchless, s);
 }
 
 }  // namespace
@@ -1195,11 +1463,11 @@ void launch_lj_nl(const Views& v, const FFDev& ff, bool fp32, int kernel, bool e
     Views w = v;
     w.payload = const_cast<void*>(pay);
     if (fp32) {
-      if (energy) launch_tile<false, true, true>(w, ff, cf, cd, false, homes, s);
-      else launch_tile<false, false, true>(w, ff, cf, cd, false, homes, s);
+      if (energy) launch_tile<false, true>(w, ff, cf, cd, homes, s);
+      else launch_tile<false, false>(w, ff, cf, cd, homes, s);
     } else {
-      if (energy) launch_tile<true, true, true>(w, ff, cf, cd, false, homes, s);
-      else launch_tile<true, false, true>(w, ff, cf, cd, false, homes, s);
+      if (energy) launch_tile<true, true>(w, ff, cf, cd, homes, s);
+      else launch_tile<true, false>(w, ff, cf, cd, homes, s);
     }
     return;
   }
@@ -1232,9 +1500,9 @@ void launch_lj(const Views& v, const FFDev& ff, bool fp32, int kernel, bool ener
     else hipLaunchKernelGGL(k_half_finish<double>, dim3(fg), dim3(256), 0, s, v);
     return;
   }
-  const bool bl = kernel == 3;   // mixed cell tile (FP64 goes to the group kernel)
-  if (energy) launch_tile<false, true>(v, ff, cf, cd, bl, homes, s);
-  else launch_tile<false, false>(v, ff, cf, cd, bl, homes, s);
+  const bool nb = kernel == 3;   // (FP64 goes to the group kernel)
+  if (energy) launch_cell<true>(v, ff, cf, cd, nb, homes, s);
+  else launch_cell<false>(v, ff, cf, cd, nb, homes, s);
 }
 
 }  // namespace mdk

@@ -42,12 +42,13 @@ __device__ inline int lanes_below(uint64_t m) {
 
 enum class Xl { Swap32, Swap16, Ror8, Mirror8, Quad2, Quad1 };
 
+// (every source lane is valid; with bound_ctrl set the move folds into the instruction that uses it)
 __device__ __forceinline__ uint32_t dpp32(uint32_t x, Xl p) {
   switch (p) {
-    case Xl::Ror8: return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xf, 0xf, false);
-    case Xl::Mirror8: return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x141, 0xf, 0xf, false);
-    case Xl::Quad2: return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4e, 0xf, 0xf, false);
-    default: return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xb1, 0xf, 0xf, false);
+    case Xl::Ror8: return (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x128, 0xf, 0xf, true);
+    case Xl::Mirror8: return (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x141, 0xf, 0xf, true);
+    case Xl::Quad2: return (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x4e, 0xf, 0xf, true);
+    default: return (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0xb1, 0xf, 0xf, true);
   }
 }
 
@@ -164,6 +165,9 @@ __device__ inline double uni(double x) {
 
 // The value of x on lane k (k wave-uniform), in scalar registers.
 __device__ inline int lane_value(int x, int k) { return __builtin_amdgcn_readlane(x, k); }
+__device__ inline float lane_value(float x, int k) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), k));
+}
 __device__ inline double lane_value(double x, int k) {
   const long long b = __double_as_longlong(x);
   const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffLL), k);
@@ -184,7 +188,7 @@ __device__ inline double box_top<double>() { return __builtin_huge_val(); }
 
 template <typename T>
 __device__ __forceinline__ T in_vgpr(T x) {
-  if constexpr (std::is_same<T, int>::value) asm volatile("" : "+v"(x));
+  if constexpr (sizeof(T) == 4) asm volatile("" : "+v"(x));
   return x;
 }
 
@@ -202,6 +206,15 @@ template <int K, typename T>
 __device__ __forceinline__ T first_lanes_min(T x) { return first_lanes_ext<K, false>(x); }
 template <int K, typename T>
 __device__ __forceinline__ T first_lanes_max(T x) { return first_lanes_ext<K, true>(x); }
+
+// LDS is written and read by one wavefront, which executes its LDS accesses in order: only the
+// compiler has to keep them so.
+__device__ __forceinline__ void lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+constexpr float kFix2F = 1.125899906842624e15f;   // 2^50
 
 template <typename P>
 struct LjPair {
@@ -297,16 +310,6 @@ __device__ __forceinline__ void add_close_pair(const double (&d)[3], double r2, 
   }
 }
 
-// x clamped to [lo, hi] (lo <= hi), for the bounding-box filter.  Fixed point: the median
-// of the three in one instruction (the compiler cannot prove lo <= hi, and a max and a min
-// are two); FP64: a max and a min.
-__device__ __forceinline__ int clamp_box(int x, int lo, int hi) {
-  int r;
-  asm("v_med3_i32 %0, %1, %2, %3" : "=v"(r) : "v"(x), "v"(lo), "v"(hi));
-  return r;
-}
-__device__ __forceinline__ double clamp_box(double x, double lo, double hi) { return min(max(x, lo), hi); }
-
 // FP32 r^2 of an exact fixed-point difference (units of 2^-50 A^2).  Written with explicit
 // fused multiply-adds so that every call site rounds identically.
 __device__ __forceinline__ float r2_fix(float dx, float dy, float dz) {
@@ -319,10 +322,10 @@ __device__ __forceinline__ float r2_fix(float dx, float dy, float dz) {
 // (r2s >= 0, so integer order is float order), so that the caller sees a band pair
 // (bmax >= lo) at one integer max per pair and settles it.  A close contact (r2s < close)
 // is not counted: near is set, and the caller evaluates it in FP64.
-// Returns r2s.  BRANCHLESS evaluates the force for every lane and zeroes it outside.
+// Returns r2s.
 // FOLD: f12 holds f12 / f6 and the caller multiplies the summed force by f6 (one type
 // pair: the force factor is then one FMA with an inline constant and no register copy).
-template <bool ENERGY, bool BRANCHLESS, bool FOLD = false>
+template <bool ENERGY, bool FOLD = false>
 __device__ __forceinline__ float pair_fix(int dqx, int dqy, int dqz, bool keep, const Band& bd, float f12,
                                           float f6, float e12, float e6, float ecut, float& ax, float& ay,
                                           float& az, double& e, double& es, double& w, int32_t& bmax,
@@ -333,18 +336,17 @@ __device__ __forceinline__ float pair_fix(int dqx, int dqy, int dqz, bool keep, 
   const bool kh = keep && r2s < bd.hi;
   near = near || (kh && lt_close);
   const bool hit = kh && !lt_close;
-  if (BRANCHLESS || hit) {
+  if (hit) {
     const float r2 = r2s * kInvFix2F;
     const float r2i = rcp_f(r2);
     const float r6 = r2i * r2i * r2i;
     const float g = FOLD ? r6 * __builtin_fmaf(f12, r6, -1.0f) : r6 * (f12 * r6 - f6);   // F . r (/ f6)
     float ffs = g * r2i;
-    if (BRANCHLESS) ffs = hit ? ffs : 0.0f;
     ax += ffs * dx;
     ay += ffs * dy;
     az += ffs * dz;
-    bmax = max(bmax, __float_as_int(BRANCHLESS ? (hit ? r2s : 0.0f) : r2s));
-    if (ENERGY && hit) {
+    bmax = max(bmax, __float_as_int(r2s));
+    if (ENERGY) {
       const float en = r6 * (e12 * r6 - e6);
       e += (double)en;
       es += (double)en - (double)ecut;
