@@ -748,9 +748,11 @@ void k_lj_cell(Views v, FFDev ff, LjPair<float> cf, LjPair<double> cd) {
               const uint32_t wide = (uint32_t)(min(i + ff.excl, c0 + ff.chain_len - 1) - first);
               const float r2s = r2_fix((float)fix_sub(fix_sub(h.x, q0.x), q.x), (float)fix_sub(fix_sub(h.y, q0.y), q.y),
                                        (float)fix_sub(fix_sub(h.z, q0.z), q.z));
+              const bool exactly = (uint32_t)(tag_index(jt) - first) > wide && r2s < cf.band_hi &&
+                                   !(r2s >= cf.close && r2s < cf.band_lo);
+              if (__builtin_amdgcn_ballot_w64(exactly) == 0) continue;   // another home's
               double px = 0.0, py = 0.0, pz = 0.0;
-              if ((uint32_t)(tag_index(jt) - first) > wide && r2s < cf.band_hi &&
-                  !(r2s >= cf.close && r2s < cf.band_lo)) {
+              if (exactly) {
                 double d[3], r2;
                 const int tt = UNI ? 0 : tag_type(pay_tag(h)) * 2 + (int)jtype;
                 if (inside_cutoff_f64(v.pos, v.N, B, i, tag_index(jt), ff.rc2, d, r2))
