@@ -69,7 +69,7 @@ def candidate_and_pair_counts(pos, box, start, M, R, rc, n_chains, chain_len):
     return candidates, pairs
 
 
-TRAFFIC_RECORD = os.path.join(ROOT, "profiles", "lj_tile_mixed_melt300k_traffic.json")
+TRAFFIC_RECORD = os.path.join(ROOT, "profiles", "lj_cell_mixed_melt300k_traffic.json")
 LJ_SOURCE = os.path.join(ROOT, "paper_1001_3764_amd", "csrc", "md_lj.hip")
 
 
@@ -150,7 +150,7 @@ def lj_roofline(N, box, rc, cand_stencil, pairs, lj_ms, kern, R, homes):
     flop = LJ_FLOP_PER_CANDIDATE * cand_canon + LJ_FLOP_PER_PAIR * pairs
     flop_stencil = LJ_FLOP_PER_CANDIDATE * cand_stencil + LJ_FLOP_PER_PAIR * pairs
     achieved = flop / (lj_ms * 1e-3) / 1e12
-    kname = "k_lj_tile" if kern in (2, 3) else "k_lj_atom"
+    kname = "k_lj_cell" if kern in (2, 3) else "k_lj_group"
     rec = counter_record("%s/R%d/K%d/H%d" % (kname, R, kern, homes))
     out = {"bound": "alu", "achieved": round(achieved, 3), "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s",
            "frac": round(achieved / PEAK_FP32_TFLOPS, 4), "traffic": rec.get("bytes_per_launch"),

@@ -509,9 +509,9 @@ void k_lj_tile(Views v, FFDev ff, LjPair<float> cf, LjPair<double> cd) {
 // goes, in the frame of the cell's first atom, to a list in LDS, which is then taken 64 at a time
 // against the homes, held wave-uniform.  The payload is in box coordinates (modulo 128 A).
 //
-// Bound: VALU issue (1,460 instructions per cell of 5.2 atoms at R = 2, about half of them pairs: 24
-// each for 27.8 steps of 64; the rest set-up, 10 windows of 35 and the sums).  The form before listed
-// every candidate's index in LDS and gathered the payload twice (1,605 instructions).  LJ pass, event
+// Bound: VALU issue (1,419 instructions per cell of 5.1 atoms at R = 2, about half of them pairs: 24 for
+// each home and 64 candidates; the rest set-up, 10 windows of 35 and the sums).  The form before listed
+// every candidate's index in LDS and gathered the payload twice (1,565 instructions).  LJ pass, event
 // timing: 300,000 atoms 159 -> 152 us; a step of 24 boxes of 453,600 atoms 272 -> 262 us, of 3,000 atoms
 // 40.0 -> 38.7 us, of 3,000,000 atoms 1,630 -> 1,618 us.  Force error against FP64 as before (rms 5.06e-7
 // over 24 melts).  Measured as well: the homes by scalar loads, no change.
