@@ -6,6 +6,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <limits>
 #include <mutex>
 #include <new>
 #include <string>
@@ -452,6 +453,8 @@ FFDev make_ffdev(const md_forcefield* ff, int chain_len) {
     }
   for (int t = 1; t < 4; ++t)
     if (d.f12[t] != d.f12[0] || d.f6[t] != d.f6[0]) d.uniform_lj = 0;
+  // the one-type forms sum forces divided by f6: with no (or hardly any) attraction they have nothing to divide by
+  if (d.f6[0] < (double)std::numeric_limits<float>::min()) d.uniform_lj = 0;
   d.rc2 = ff->rc * ff->rc;
   d.kb = ff->kb;
   d.b0 = ff->b0;

@@ -1,0 +1,40 @@
+"""GPU parity at the limits of the force field that the set-up accepts."""
+import numpy as np
+import pytest
+
+import oracle as O
+from pe_melt import make_melt
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"mixed": 1e-5, "fp64": 1e-10}   # max force error over the oracle's RMS force (FP32 / FP64 forces)
+
+
+def system(ff, m, precision, R, kernel, **kw):
+    from paper_1001_3764_amd.md import MDSystem
+    print("system: N=%d box=%s precision=%s R=%d kernel=%d" % (m.n_atoms, m.box, precision, R, kernel), flush=True)
+    return MDSystem(ff, [m.n_chains], m.box[None, :], [0.0], m.pos, m.vel, m.types, chain_len=m.chain_len,
+                    precision=precision, cell_div=R, lj_kernel=kernel, **kw)
+
+
+def norm_err(f, ref):
+    return float(np.max(np.sqrt(np.sum((f - ref) ** 2, axis=0))) / np.sqrt(np.mean(np.sum(ref ** 2, axis=0))))
+
+
+@pytest.mark.parametrize("precision,R,kernel,skin", [
+    ("mixed", 1, 1, 0.0), ("mixed", 2, 1, 0.0), ("mixed", 2, 2, 0.0), ("mixed", 2, 3, 0.0), ("mixed", 2, 6, 0.0),
+    ("mixed", 2, 4, 0.8), ("mixed", 2, 5, 0.8), ("fp64", 2, 1, 0.0), ("fp64", 2, 4, 0.8), ("fp64", 2, 5, 0.8)])
+def test_no_lennard_jones(ff, precision, R, kernel, skin):
+    """epsilon = 0 for both types: the Lennard-Jones force and energies are exactly zero, the rest is the bonded terms."""
+    ff = dict(ff, epsilon=(0.0, 0.0))
+    m = make_melt(50, chain_len=24, density=0.80, T=500.0, seed_melt=21, seed_vel=22, jitter=0.05)
+    s = system(ff, m, precision, R, kernel, **({"nl_skin": skin} if skin else {}))
+    f, flj, e = s.forces(), s.forces(lj_only=True), s.energies()[0]
+    s.step(3)
+    p, v = s.state()
+    s.close()
+    fo, eo = O.bonded(ff, m.pos, m.box, m.chain_len)
+    assert not flj.any() and e["e_lj"] == 0.0 and e["e_lj_shifted"] == 0.0
+    assert norm_err(f, fo) <= TOL[precision]
+    assert e["virial"] == pytest.approx(eo["virial_bonded"], rel=2e-6 if precision == "mixed" else 1e-12, abs=1e-2)
+    assert np.isfinite(p).all() and np.isfinite(v).all()
