@@ -428,7 +428,9 @@ LjPair<P> make_pair(const FFDev& ff) {
   double s6 = 0.0;
   for (int t = 0; t < 4; ++t)
     if (ff.e6[t] > 0.0) s6 = s6 > 0.0 ? std::min(s6, ff.e12[t] / ff.e6[t]) : ff.e12[t] / ff.e6[t];
-  c.close = (float)(kCloseSigma * kCloseSigma * std::cbrt(s6) * kFix * kFix);
+  // (at most the band: with a cutoff below the bound every pair inside it is a close contact or in the
+  // band, and [close, band_lo) is empty, as the kernels' range test on it needs)
+  c.close = std::min((float)(kCloseSigma * kCloseSigma * std::cbrt(s6) * kFix * kFix), c.band_lo);
   return c;
 }
 

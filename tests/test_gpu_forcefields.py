@@ -38,3 +38,33 @@ def test_no_lennard_jones(ff, precision, R, kernel, skin):
     assert norm_err(f, fo) <= TOL[precision]
     assert e["virial"] == pytest.approx(eo["virial_bonded"], rel=2e-6 if precision == "mixed" else 1e-12, abs=1e-2)
     assert np.isfinite(p).all() and np.isfinite(v).all()
+
+
+@pytest.mark.parametrize("precision,R,kernel,skin", [
+    ("mixed", 1, 1, 0.0), ("mixed", 2, 1, 0.0), ("mixed", 1, 2, 0.0), ("mixed", 2, 2, 0.0), ("mixed", 2, 3, 0.0),
+    ("mixed", 2, 6, 0.0), ("mixed", 2, 4, 0.3), ("mixed", 2, 5, 0.3), ("fp64", 2, 1, 0.0)])
+@pytest.mark.parametrize("two_types", [False, True])
+def test_cutoff_below_the_close_contacts(ff, two_types, precision, R, kernel, skin):
+    """A cutoff below 0.75 sigma, where every pair is a close contact, in a squeezed melt, with pairs so near the
+    cutoff that FP32 cannot tell their side (rc is set by the distance of a pair of the configuration)."""
+    import dataclasses
+    m = make_melt(40, chain_len=24, density=0.80, T=500.0, seed_melt=31, seed_vel=32, jitter=0.05)
+    m = dataclasses.replace(m, pos=np.ascontiguousarray(m.pos * 0.7), box=m.box * 0.7)
+    from scipy.spatial import cKDTree
+    tree = cKDTree(np.mod(m.pos.T, m.box), boxsize=m.box)
+    i, j = tree.query_pairs(2.4, output_type="ndarray").T
+    far = (i // m.chain_len != j // m.chain_len) | (np.abs(i - j) > 2)
+    d = m.pos[:, i] - m.pos[:, j]
+    d -= m.box[:, None] * np.round(d / m.box[:, None])
+    r = np.sort(np.sqrt(np.sum(d * d, axis=0))[far])
+    ff = dict(ff, rc=float(r[-1] * (1.0 + 2e-7)))
+    if two_types:
+        ff.update(sigma=(3.47, 3.70), epsilon=(0.0951, 0.1200))
+    s = system(ff, m, precision, R, kernel, **({"nl_skin": skin} if skin else {}))
+    flj, e = s.forces(lj_only=True), s.energies()[0]
+    s.close()
+    fo, eo = O.lj_brute(ff, m.pos, m.types, m.box, m.chain_len)
+    err = norm_err(flj, fo)
+    print("rc %.6f, %d pairs, force error %.3e" % (ff["rc"], far.sum(), err))
+    assert err <= TOL[precision]
+    assert e["e_lj"] == pytest.approx(eo["e_lj"], rel=2e-6 if precision == "mixed" else 1e-12)
