@@ -32,7 +32,10 @@ constexpr int kCap = 160;            // filtered candidates a wave holds in LDS 
 template <bool FP64>
 constexpr int kGroupEu = FP64 ? 5 : 4;   // waves per SIMD the registers are held to
 constexpr int kChunkWindows = 64;    // 64-candidate windows whose run starts are marked at a time
-constexpr double kGap = 1e-3;        // A added to every reach and to the filter: their FP32 rounding
+// Added to every reach and to the filter for their FP32 rounding (and what the order along x leaves open,
+// 1e-6 of a cell): in the mixed form, whose coordinates round to 2^-17 A at most, in A; in FP64, whose lengths
+// may have any scale, as a part of the cutoff.
+constexpr float kGap = 1e-3f, kGapOfRc = 1e-4f;
 
 struct Cand32 {      // mixed: offsets from the group's first atom in 2^-25 A, biased by 2^31
   uint32_t x, y, z;
@@ -64,7 +67,7 @@ struct Geo<true> {
   __device__ static Off origin(Off ref) { return -ref; }
   __device__ static double rel(double x, Off o) { return x + o; }
   __device__ static float filt(double u) { return (float)u; }
-  __device__ static double far() { return 1.0e6; }
+  __device__ static double far() { return 1.0e150; }     // (its square is finite)
   __device__ static Cand cand(double x, double y, double z, int32_t tag) {
     return Cand{x, y, z, __longlong_as_double((long long)tag)};
   }
@@ -207,7 +210,7 @@ void k_lj_group(Views v, FFDev ff, LjPair<float> cf, LjPair<double> cd) {
             // in tag units; a slot without a home excludes every candidate
             window[ln] = mine ? make_int2(lo << 4, (int)((span << 4) | 15u)) : make_int2(0, -1);
           }
-          // x order inside the group (up to the key's 2^-32 of a cell: kGap covers it)
+          // x order inside the group (up to the key's 1e-6 of a cell: the gap covers it)
           xhi = lane_value_f(fx, h1 - 1);
           xe = lane_value_f(dx0, h1 - 1);
           ylo = ext<K, false>(mine ? fy : G::kZero);
@@ -324,7 +327,8 @@ void k_lj_group(Views v, FFDev ff, LjPair<float> cf, LjPair<double> cd) {
         };
         // ---- the candidates: one pass per periodic image along x that the group reaches ----
         int im = 0, im_left = -1;   // this pass's image; bit 0 / 1: image -1 / +1 still to do
-        const float rc = __builtin_amdgcn_sqrtf((float)ff.rc2) + (float)kGap;
+        const float gap = FP64 ? kGapOfRc * __builtin_amdgcn_sqrtf((float)ff.rc2) : kGap;
+        const float rc = __builtin_amdgcn_sqrtf((float)ff.rc2) + gap;
         const float rcf = rc * rc * (G::kUnit * G::kUnit);
         do {
           // the runs, one stencil row per lane
@@ -335,10 +339,10 @@ void k_lj_group(Views v, FFDev ff, LjPair<float> cf, LjPair<double> cd) {
           const float gz = oz > 0 ? (float)oz * e2 - (zr + (zhi - G::kZero) * iu)
                                   : (zr + (zlo - G::kZero) * iu) - (float)(oz + 1) * e2;
           // (in the group's own row and layer both forms are negative)
-          const float hy = fmaxf(gy - (float)kGap, 0.0f), hz = fmaxf(gz - (float)kGap, 0.0f);
+          const float hy = fmaxf(gy - gap, 0.0f), hz = fmaxf(gz - gap, 0.0f);
           const float left = rc * rc - hy * hy - hz * hz;
           const bool inrow = ln < W * W && left > 0.0f;
-          const float reach = __builtin_amdgcn_sqrtf(fmaxf(left, 0.0f)) + (float)kGap, ie0 = rcp_f(e0);
+          const float reach = __builtin_amdgcn_sqrtf(fmaxf(left, 0.0f)) + gap, ie0 = rcp_f(e0);
           const int low = kx + (int)floorf((xr - reach) * ie0);
           const int high = kx + (int)floorf((xr + xe + reach) * ie0);
           if (im_left < 0)

@@ -68,3 +68,23 @@ def test_cutoff_below_the_close_contacts(ff, two_types, precision, R, kernel, sk
     print("rc %.6f, %d pairs, force error %.3e" % (ff["rc"], far.sum(), err))
     assert err <= TOL[precision]
     assert e["e_lj"] == pytest.approx(eo["e_lj"], rel=2e-6 if precision == "mixed" else 1e-12)
+
+
+@pytest.mark.parametrize("R,kernel", [(1, 1), (2, 1), (2, 2), (3, 1)])
+@pytest.mark.parametrize("power", [-33, 12, 18])
+def test_other_units_of_length(ff, power, R, kernel):
+    """Every length multiplied by a power of two (FP64, whose lengths have no range of their own): the same
+    system in another unit, so the forces scale by its inverse."""
+    import dataclasses
+    u = 2.0 ** power
+    m = make_melt(50, chain_len=24, density=0.80, T=500.0, seed_melt=21, seed_vel=22, jitter=0.05)
+    fo, eo = O.lj_brute(ff, m.pos, m.types, m.box, m.chain_len)
+    ff = dict(ff, sigma=tuple(u * x for x in ff["sigma"]), rc=u * ff["rc"], b0=u * ff["b0"], kb=ff["kb"] / (u * u))
+    m = dataclasses.replace(m, pos=u * m.pos, box=u * m.box)
+    s = system(ff, m, "fp64", R, kernel)
+    flj, e = s.forces(lj_only=True), s.energies()[0]
+    s.close()
+    err = norm_err(u * flj, fo)
+    print("force error %.3e" % err)
+    assert err <= TOL["fp64"]
+    assert e["e_lj"] == pytest.approx(eo["e_lj"], rel=1e-12)
