@@ -51,7 +51,7 @@ struct Geo<false> {
   using Off = int32_t;    // offset added to a payload coordinate
   static constexpr float kUnit = 1.0f / kInvFixF;      // filter units per A
   static constexpr float kZero = 2147483648.0f;         // the group's first atom in filter units
-  __device__ static Off origin(Off ref) { return (Off)(0x80000000u - (uint32_t)ref); }
+  __device__ static Off origin(Off ref, double) { return (Off)(0x80000000u - (uint32_t)ref); }
   __device__ static uint32_t rel(int x, Off o) { return (uint32_t)x + (uint32_t)o; }
   __device__ static float filt(uint32_t u) { return (float)u; }
   __device__ static uint32_t far() { return 0u; }        // 64 A from the group's first atom
@@ -64,7 +64,9 @@ struct Geo<true> {
   using Off = double;
   static constexpr float kUnit = 1.0f;
   static constexpr float kZero = 0.0f;
-  __device__ static Off origin(Off ref) { return -ref; }
+  // The group's first coordinate rounded to a multiple of the box edge's last place, so that the origin of
+  // a periodic image, one edge further, is exact: pairs across an edge lose nothing to the box's length.
+  __device__ static Off origin(Off ref, double L) { return uni(L - (ref + L)); }
   __device__ static double rel(double x, Off o) { return x + o; }
   __device__ static float filt(double u) { return (float)u; }
   __device__ static double far() { return 1.0e150; }     // (its square is finite)
@@ -189,9 +191,9 @@ void k_lj_group(Views v, FFDev ff, LjPair<float> cf, LjPair<double> cd) {
           const int hcell = v.scell[p0 + hl] - row0;
           const int32_t i = tag_index(pay_tag(hq));
           const Off x0 = lane_value(hq.x, h0), y0 = lane_value(hq.y, h0), z0 = lane_value(hq.z, h0);
-          ox0 = G::origin(x0);
-          oy0 = G::origin(y0);
-          oz0 = G::origin(z0);
+          ox0 = G::origin(x0, B.L[0]);
+          oy0 = G::origin(y0, B.L[1]);
+          oz0 = G::origin(z0, B.L[2]);
           const auto ux = G::rel(hq.x, ox0), uy = G::rel(hq.y, oy0), uz = G::rel(hq.z, oz0);
           const float fx = G::filt(ux), fy = G::filt(uy), fz = G::filt(uz);
           // (the cell distance tells apart what the offset modulo 128 A cannot)
@@ -327,7 +329,7 @@ void k_lj_group(Views v, FFDev ff, LjPair<float> cf, LjPair<double> cd) {
         };
         // ---- the candidates: one pass per periodic image along x that the group reaches ----
         int im = 0, im_left = -1;   // this pass's image; bit 0 / 1: image -1 / +1 still to do
-        const float gap = FP64 ? kGapOfRc * __builtin_amdgcn_sqrtf((float)ff.rc2) : kGap;
+        const float gap = FP64 ? lane_value(kGapOfRc * __builtin_amdgcn_sqrtf((float)ff.rc2), 0) : kGap;
         const float rc = __builtin_amdgcn_sqrtf((float)ff.rc2) + gap;
         const float rcf = rc * rc * (G::kUnit * G::kUnit);
         do {
@@ -364,7 +366,7 @@ void k_lj_group(Views v, FFDev ff, LjPair<float> cf, LjPair<double> cd) {
           total = uni(total);
           const uint64_t some = __builtin_amdgcn_ballot_w64(n > 0);
           Off sx;
-          if constexpr (FP64) sx = ox0 + (double)im * B.L[0];
+          if constexpr (FP64) sx = uni(ox0 + (double)im * B.L[0]);
           else sx = (Off)((uint32_t)ox0 + (uint32_t)im * (uint32_t)Q.L_q[0]);
           if (n > 0) {
             Run<Off> r;

@@ -88,3 +88,49 @@ def test_other_units_of_length(ff, power, R, kernel):
     print("force error %.3e" % err)
     assert err <= TOL["fp64"]
     assert e["e_lj"] == pytest.approx(eo["e_lj"], rel=1e-12)
+
+
+@pytest.mark.parametrize("R,kernel", [(1, 1), (2, 2), (3, 1)])
+@pytest.mark.parametrize("axis", [0, 1, 2])
+def test_pairs_across_the_edge_of_a_long_box(ff, axis, R, kernel):
+    """FP64, a melt that lies across the edge of a box 1,000 A long.  Each pair's force is the one of the given
+    positions to the rounding of differences of at most 64 A: per atom, the error is at most
+    sum_j |F_ij| (14 delta / r + 32 ulp), where 14 bounds -d ln F / d ln r away from the force's zero, as computed
+    here from F's two terms, and delta = 3 roundings of 2^-48 A (half an ulp below 64 A)."""
+    import dataclasses
+    m = make_melt(30, chain_len=24, density=0.80, T=500.0, seed_melt=41, seed_vel=42, jitter=0.05)
+    p = m.pos.reshape(3, -1, m.chain_len)
+    d = np.diff(p, axis=2)
+    d -= m.box[:, None, None] * np.round(d / m.box[:, None, None])
+    flat = np.concatenate([p[:, :, :1], p[:, :, :1] + np.cumsum(d, axis=2)], axis=2).reshape(3, -1)
+    box = np.array([80.0, 80.0, 80.0])   # (whole chains stick out of the original box: no overlaps across the edges)
+    box[axis] = 1000.3
+    flat[axis] -= 0.5 * m.box[axis]
+    pos = np.mod(flat, box[:, None])
+    pos[pos >= box[:, None]] = 0.0
+    m = dataclasses.replace(m, pos=np.ascontiguousarray(pos), box=box)
+    s = system(ff, m, "fp64", R, kernel)
+    f = s.forces(lj_only=True)
+    s.close()
+    from scipy.spatial import cKDTree
+    i, j = cKDTree(pos.T, boxsize=box).query_pairs(ff["rc"], output_type="ndarray").T
+    k = (i // m.chain_len != j // m.chain_len) | (np.abs(i - j) > ff["excl_depth"])
+    i, j = i[k], j[k]
+    X = np.longdouble
+    d = pos.astype(X)[:, i] - pos.astype(X)[:, j]
+    d -= box.astype(X)[:, None] * np.rint(d / box.astype(X)[:, None])
+    r2 = np.sum(d * d, axis=0)
+    s6 = (X(ff["sigma"][0]) ** 2 / r2) ** 3
+    a, b = 48 * X(ff["epsilon"][0]) * s6 * s6 / r2, 24 * X(ff["epsilon"][0]) * s6 / r2
+    fo, bound = np.zeros((3, m.n_atoms), X), np.zeros(m.n_atoms, X)
+    term = (a + b) * np.sqrt(r2) * (14 * X(3 * 2.0 ** -48) / np.sqrt(r2) + 32 * X(2.0 ** -52))
+    for q in range(3):
+        np.add.at(fo[q], i, (a - b) * d[q])
+        np.add.at(fo[q], j, -(a - b) * d[q])
+    np.add.at(bound, i, term)
+    np.add.at(bound, j, term)
+    err = np.sqrt(np.sum((f - fo) ** 2, axis=0))
+    crosses = np.abs(pos[axis][i] - pos[axis][j]) > 500.0
+    print("%d of %d pairs across the edge; error over bound %.3f" % (crosses.sum(), i.size, float(np.max(err / bound))))
+    assert crosses.sum() > 1000
+    assert np.all(err <= bound)
