@@ -239,6 +239,11 @@ GroupDev group_work(const md_forcefield* ff, const md_config* cfg, int64_t n, co
   // stay below 64 A (payload_ok: (R + 2) edge < 63 A, so the cap is at least edge - 1)
   g.cap = ff->rc;
   if (cfg->precision == MD_PREC_MIXED) g.cap = std::min(ff->rc, 62.0 - ff->rc - B.edge[0]);
+  // The gap covers the FP32 rounding of reaches and filter (and what the order along x leaves open, 1e-6 of a
+  // cell): in the mixed form, whose coordinates round to 2^-17 A at most, in A; in FP64, whose lengths
+  // may have any scale, as a part of the cutoff.
+  g.gap = cfg->precision == MD_PREC_MIXED ? 1e-3f : (float)(1e-4 * ff->rc);
+  g.rc_gap = (float)ff->rc + g.gap;
   return g;
 }
 

@@ -32,10 +32,6 @@ constexpr int kCap = 160;            // filtered candidates a wave holds in LDS 
 template <bool FP64>
 constexpr int kGroupEu = FP64 ? 5 : 4;   // waves per SIMD the registers are held to
 constexpr int kChunkWindows = 64;    // 64-candidate windows whose run starts are marked at a time
-// Added to every reach and to the filter for their FP32 rounding (and what the order along x leaves open,
-// 1e-6 of a cell): in the mixed form, whose coordinates round to 2^-17 A at most, in A; in FP64, whose lengths
-// may have any scale, as a part of the cutoff.
-constexpr float kGap = 1e-3f, kGapOfRc = 1e-4f;
 
 struct Cand32 {      // mixed: offsets from the group's first atom in 2^-25 A, biased by 2^31
   uint32_t x, y, z;
@@ -329,8 +325,7 @@ void k_lj_group(Views v, FFDev ff, LjPair<float> cf, LjPair<double> cd) {
         };
         // ---- the candidates: one pass per periodic image along x that the group reaches ----
         int im = 0, im_left = -1;   // this pass's image; bit 0 / 1: image -1 / +1 still to do
-        const float gap = FP64 ? lane_value(kGapOfRc * __builtin_amdgcn_sqrtf((float)ff.rc2), 0) : kGap;
-        const float rc = __builtin_amdgcn_sqrtf((float)ff.rc2) + gap;
+        const float gap = Q.gap, rc = Q.rc_gap;
         const float rcf = rc * rc * (G::kUnit * G::kUnit);
         do {
           // the runs, one stencil row per lane

@@ -75,6 +75,7 @@ struct GroupDev {
   int32_t L_q[3];                 // edges in fixed-point units, modulo 2^32
   double inv_slots, inv_m1;       // 1 / slots, 1 / M[1]
   double cap;                     // A: extent along x of a group of home atoms
+  float gap, rc_gap;              // added to every reach; the cutoff plus it
 };
 
 // Force-field constants in the form the kernels use (built on the host).
