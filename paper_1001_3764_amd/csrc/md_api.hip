@@ -732,6 +732,7 @@ md_status autotune(md_ctx* c, const md_config* cfg, int* bestR, int* bestK, int*
     }
     Rs.erase(std::remove_if(Rs.begin(), Rs.end(), [](int R) { return R > kTileMaxR; }), Rs.end());
   } else if (cfg->lj_kernel) Ks.push_back(cfg->lj_kernel);
+  else if (cfg->cell_div > kTileMaxR) Ks.push_back(MD_LJ_ATOM);   // the only kernel these grids take
   else {
     // (FP64: every kernel 1..3 is the group kernel)
     Ks.push_back(MD_LJ_CELLTILE);

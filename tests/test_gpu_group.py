@@ -101,3 +101,18 @@ def test_sparse_rows(ff, precision, scale):
     s.close()
     print("force error %.3e, LJ %.3e" % (err, err_lj))
     assert err <= TOL[precision] and err_lj <= TOL[precision]
+
+
+@pytest.mark.parametrize("precision", ["mixed", "fp64"])
+@pytest.mark.parametrize("R", [2, 3])
+def test_tuned_choice_is_accepted(ff, R, precision):
+    """What md_tuning reports for a given cell_div sets up the same context when it is given."""
+    m = make_melt(10, density=0.80, T=500.0, seed_melt=1000, seed_vel=1001, jitter=0.05)
+    s = system(ff, [m], precision, R, 0)
+    r, k, h = s.tuning(homes=True)
+    f = s.forces()
+    s.close()
+    assert r == R
+    s = system(ff, [m], precision, r, k, tile_homes=h)
+    assert s.tuning(homes=True) == (r, k, h) and np.array_equal(s.forces(), f)
+    s.close()
