@@ -327,6 +327,12 @@ Plan make_plan(const md_forcefield* ff, const md_config* cfg, int R, int kernel)
     }
     p.boxes.push_back(B);
   }
+  // kSplit waves per group pay where one wave each would leave the chip idle, so they go by the groups of all
+  // such boxes together.
+  int64_t split = 0;
+  for (const GroupDev& g : p.groups) split += g.waves == kSplit ? g.items : 0;
+  if (split > kSplitItems)
+    for (GroupDev& g : p.groups) g.waves = 1;
   p.n_cell_blocks = (int32_t)cblk;
   p.nl_entries = nle;
   p.N = atom;

@@ -274,7 +274,7 @@ void launch_ree(const Views& v, int b, int64_t n_chains, int chain_len, bool ref
 void launch_lj_group(const Views& v, const FFDev& ff, bool fp32, bool energy, hipStream_t s);
 constexpr int kGroupPad = 16;   // a box's group blocks are padded to a multiple of this
 constexpr int kSplit = 4;       // wavefronts that share a group in boxes of few groups
-constexpr int kSplitItems = 2048;   // at most this many groups
+constexpr int kSplitItems = 2048;   // at most this many groups in all such boxes
 constexpr int kGroupHomes = 8;  // home atoms per group
 
 constexpr int kTileHomesMixed = 8;   // home atoms per pass of a mixed cell-tile wave

@@ -116,3 +116,23 @@ def test_tuned_choice_is_accepted(ff, R, precision):
     s = system(ff, [m], precision, r, k, tile_homes=h)
     assert s.tuning(homes=True) == (r, k, h) and np.array_equal(s.forces(), f)
     s.close()
+
+
+@pytest.mark.parametrize("precision", ["mixed", "fp64"])
+@pytest.mark.parametrize("boxes", [4, 5])
+def test_batch_on_either_side_of_the_split(ff, boxes, precision):
+    """Boxes of 448 groups each: four have fewer than 2,048 together (several wavefronts per group), five more."""
+    melts = [make_melt(10, density=0.80, T=400.0, seed_melt=700 + b, seed_vel=701, jitter=0.05) for b in range(boxes)]
+    s = system(ff, melts, precision, 2, 1)
+    f, e = s.forces(), s.energies()
+    s.step(2)
+    p, v = s.state()
+    s.close()
+    for b, m in enumerate(melts):
+        fo, eo = O.forces(ff, m.pos, m.types, m.box, 300)
+        assert norm_err(f[:, 3000 * b:3000 * (b + 1)], fo) <= TOL[precision]
+        assert e[b]["e_lj"] == pytest.approx(eo["e_lj"], rel=2e-6 if precision == "mixed" else 1e-12)
+    s = system(ff, melts, precision, 2, 1)
+    s.step(2)
+    assert all(np.array_equal(x, y) for x, y in zip(s.state(), (p, v)))   # the same every run
+    s.close()
