@@ -494,7 +494,8 @@ int64_t small_path(const Plan& p, int64_t* max_atoms) {
     lds = std::max(lds, small_lds_bytes(B.n_atoms, B.n_cells));
   }
   const bool ok = !p.nl_cap && (p.group || p.prec == MD_PREC_MIXED) && !p.l1_bd && !p.l1_lj &&
-                  *max_atoms <= kSmallAtoms && lds <= kSmallLds;
+                  *max_atoms <= kSmallAtoms && lds <= kSmallLds &&
+                  (p.n_boxes <= kSmallBoxes || p.N >= kSmallMean * p.n_boxes);
   return ok ? lds : 0;
 }
 

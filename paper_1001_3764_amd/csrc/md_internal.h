@@ -248,6 +248,8 @@ void launch_reduce(const Views& v, bool energy, bool update, const StepOpts& o, 
 // the last kernel of a run of steps (reduction with the energies, launch_finalize)
 constexpr int64_t kSmallAtoms = 3072;       // largest box that takes them (measured: at the kernels)
 constexpr int64_t kSmallLds = 96 << 10;     // and its LDS
+constexpr int64_t kSmallBoxes = 512;        // of more boxes than these, those of kSmallMean atoms on average
+constexpr int64_t kSmallMean = 512;
 int64_t small_lds_bytes(int64_t n_atoms, int64_t n_cells);
 void launch_small_begin(const Views& v, bool kick, const StepOpts& o, const FFDev& ff, bool fp32, int64_t max_atoms,
                         int64_t lds, hipStream_t s);

@@ -952,9 +952,11 @@ __global__ void k_clear_pending(double* thermo, int n_boxes, int lf) {
 // eight, this path against the separate kernels: FP64 at 1,800 atoms 40.8 and 48.1, at 3,000 44.9
 // and 46.6; mixed (R = 2) 35.3 and 39.7, 40.0 and 41.3.  With four atoms per thread above 3,072 it
 // lost: FP64 at 3,600 atoms 45.6 and 44.3, at 3,900 52.6 and 47.9; mixed 43.2 and 42.4, 42.1 and
-// 41.0.  So the line is at three per thread.  In batches of 3,000-atom boxes mixed gains at every
-// count (64 boxes: 123 and 130); FP64 gains at 64 (268 and 274) but loses 1.5-2% at 4 to 16
-// boxes (16: 95.1 and 93.7).
+// 41.0.  So the line is at three per thread.  In batches it gains at every count (3,000 atoms, R = 2: 16
+// boxes mixed 68.8 and 74.4, FP64 77.7 and 81.9; 1,024 boxes mixed 1,629 and 1,716, FP64 2,102 and 2,205),
+// except that past two work-groups per CU (512 boxes) they come in rounds that take their latency however
+// little a box holds: at 128 atoms 512 boxes 57.9 and 63.0 (FP64, R = 1), 1,024 98.9 and 96.8, 4,096 346 and
+// 292; at 512 atoms 4,096 boxes 1,221 and 1,232.
 //   k_small_begin  the pending reduction (thermo slot kThPending), update, drift, wrap, cell counts in
 //                  LDS, scan, cell lists in LDS, ranks, ordered lists and payload
 //   k_small_end    after the last step of a call: the reduction with the energies, what is pending

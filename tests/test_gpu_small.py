@@ -63,3 +63,24 @@ def test_batch_of_small_boxes(ff):
         assert a.energies()[0] == e[b]
         a.close()
         at += m.n_atoms
+
+
+@pytest.mark.parametrize("precision,kernel", [("mixed", 2), ("fp64", 1)])
+@pytest.mark.parametrize("boxes,chains", [(512, 8), (513, 8), (513, 32)])
+def test_many_boxes(ff, boxes, chains, precision, kernel):
+    """Either side of the line for batches (513 boxes of 128 atoms take the separate kernels, of 512 atoms not)."""
+    from paper_1001_3764_amd.md import MDSystem
+    m = make_melt(chains, chain_len=16, density=0.09 * chains / 8, T=400.0, seed_melt=81, seed_vel=82, jitter=0.05)
+    vel = np.tile(m.vel, (1, boxes)) * np.repeat(1.0 + 0.1 * np.cos(np.arange(boxes)), m.n_atoms)
+    args = (ff, [m.n_chains] * boxes, np.tile(m.box, (boxes, 1)), [330.0] * boxes, np.tile(m.pos, (1, boxes)), vel,
+            np.tile(m.types, boxes))
+    kw = dict(chain_len=16, precision=precision, cell_div=1, lj_kernel=kernel)
+    print("%d boxes of %d atoms %s" % (boxes, m.n_atoms, kw), flush=True)
+    a, b = MDSystem(*args, use_graph=True, **kw), MDSystem(*args, use_graph=False, **kw)
+    a.step(11)
+    b.step_timed(11)
+    for x, y in zip(a.state(), b.state()):
+        assert np.array_equal(x, y)
+    assert a.energies() == b.energies()
+    a.close()
+    b.close()
