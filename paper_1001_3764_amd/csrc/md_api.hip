@@ -219,19 +219,41 @@ bool group_kernel(const md_config* cfg, int kernel) {
   return kernel == MD_LJ_ATOM || (cfg->precision == MD_PREC_FP64 && (kernel == MD_LJ_CELLTILE || kernel == MD_LJ_CELLTILE_NB));
 }
 
+// Groups of `homes` atoms per row of cells, evenly filled (a row of a melt holds its mean +- a few per cent).
+int32_t row_groups(int64_t n, const BoxDev& B, int homes) {
+  return (int32_t)std::ceil(1.04 * (double)n / ((double)B.M[1] * B.M[2]) / homes + 0.25);
+}
+
 // Work of the group kernel in box B of n atoms: `slots` waves per row of cells, each taking every
-// slots-th group of the row (a row of a melt holds its mean +- a few per cent; fuller rows give
-// some waves a second group), on at most one block per 4 atoms (their energy partials live in the
-// bins' scratch, see carve) plus the padding.
-GroupDev group_work(const md_forcefield* ff, const md_config* cfg, int64_t n, const BoxDev& B) {
+// slots-th group of the row (fuller rows give some waves a second group), on at most one block per 4
+// atoms (their energy partials live in the bins' scratch, see carve) plus the padding.  split: a box of few
+// groups, whose time is that of its longest block; kSplit waves share a group.
+//
+// Where the box is emptier than a melt, the atoms may lie in few of its rows (a droplet, a film), which then hold
+// many times the mean, or thinly in all of them, too far apart for groups of 8.  A row's groups past its
+// slots go to blocks of other rows, `passes` times (an empty visit costs two loads).
+//   Below 1/50 of a melt's density: 300,000 atoms as a droplet in a box of 6 times their edges, R = 1, FP64
+//   1,021 -> 302 us a step, mixed 863 -> 280 (one lane per atom 672 and 611); gases of 1/16 and 1/34 lost
+//   6-12% to it.
+//   Boxes of few groups, below half of it and too thin for 8 homes within rc: one wave per group of 2, on up to
+//   2,048 blocks (the one-level reduction's; their partials take less than the observables' share of the
+//   scratch).  3,000 atoms, FP64, R = 2, us a step: as a droplet in a box of twice their edges 52.4 -> 42.7, at
+//   0.02 g/cm^3 60.4 -> 51.3, at 0.3 47.5 -> 42.6 (a wave per cell 44.9, 48.0 and 42.8).
+GroupDev group_work(const md_forcefield* ff, const md_config* cfg, int64_t n, const BoxDev& B, bool split) {
   GroupDev g{};
   const int64_t rows = (int64_t)B.M[1] * B.M[2];
-  const double per_row = (double)n / (double)rows;
-  g.slots = (int32_t)std::ceil(1.04 * per_row / kGroupHomes + 0.25);
+  const double sigma = 0.5 * (ff->sigma[0] + ff->sigma[1]);
+  const double fill = (double)n / (kMeltDensity / (sigma * sigma * sigma) * B.L[0] * B.L[1] * B.L[2]);
+  const bool thin = split && fill < 0.5 && (kGroupHomes - 1) * B.L[0] * (double)rows / (double)n > ff->rc;
+  int64_t most = std::max<int64_t>(n / 4, 1);
+  if (thin) most = std::max(most, std::min<int64_t>(n, kReduceChunk));
+  g.waves = split && !thin ? kSplit : 1;
+  g.homes = thin ? 2 : kGroupHomes;
+  g.passes = thin ? 3 : (fill < 0.02 ? 8 : 1);
+  g.slots = row_groups(n, B, g.homes);
   g.items = (int32_t)(rows * g.slots);
-  const int64_t most = std::max<int64_t>(n / 4, 1);
+  g.shift = (int32_t)(rows / g.passes);
   g.blocks = (int32_t)((std::min<int64_t>(g.items, most) + kGroupPad - 1) / kGroupPad * kGroupPad);
-  g.waves = g.items <= kSplitItems ? kSplit : 1;
   g.inv_slots = 1.0 / (double)g.slots;
   g.inv_m1 = 1.0 / (double)B.M[1];
   for (int d = 0; d < 3; ++d) g.L_q[d] = fix_coord(B.L[d]);
@@ -315,24 +337,25 @@ Plan make_plan(const md_forcefield* ff, const md_config* cfg, int R, int kernel)
     atom += n;
     cell += nc;
     blk += (n + kAtomBlock - 1) / kAtomBlock;
-    if (p.group) {
-      p.groups.push_back(group_work(ff, cfg, n, B));
-      lblk += p.groups.back().blocks;
-    } else {
-      lblk += lj_blocks_for_box(kernel, n, nc);
-    }
+    if (!p.group) lblk += lj_blocks_for_box(kernel, n, nc);
     if (nl) {
       cblk += (nc + kTileWaves - 1) / kTileWaves;
       nle += (kernel == MD_LJ_NLIST_TILE ? nc : (n + 63) / 64 * 64) * (int64_t)p.nl_cap;
     }
     p.boxes.push_back(B);
   }
-  // kSplit waves per group pay where one wave each would leave the chip idle, so they go by the groups of all
-  // such boxes together.
-  int64_t split = 0;
-  for (const GroupDev& g : p.groups) split += g.waves == kSplit ? g.items : 0;
-  if (split > kSplitItems)
-    for (GroupDev& g : p.groups) g.waves = 1;
+  if (p.group) {
+    // kSplit waves per group pay where one wave each would leave the chip idle, so they go by the groups of all
+    // boxes of few groups together
+    auto groups = [](const BoxDev& B) { return (int64_t)B.M[1] * B.M[2] * row_groups(B.n_atoms, B, kGroupHomes); };
+    int64_t few = 0;
+    for (const BoxDev& B : p.boxes) few += groups(B) <= kSplitItems ? groups(B) : 0;
+    for (BoxDev& B : p.boxes) {
+      B.lj_blk_off = (int32_t)lblk;
+      p.groups.push_back(group_work(ff, cfg, B.n_atoms, B, few <= kSplitItems && groups(B) <= kSplitItems));
+      lblk += p.groups.back().blocks;
+    }
+  }
   p.n_cell_blocks = (int32_t)cblk;
   p.nl_entries = nle;
   p.N = atom;

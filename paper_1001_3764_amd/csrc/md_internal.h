@@ -70,8 +70,10 @@ struct BoxDev {
 
 // Per box, for the group kernel (md_group.hip).
 struct GroupDev {
-  int32_t slots, items, blocks;   // work items per row of cells and in all; blocks of this box
+  int32_t slots, items, blocks;   // work items per row of cells and in all, per pass; blocks of this box
   int32_t waves;                  // wavefronts per group: 1, or kSplit in small boxes
+  int32_t homes;                  // home atoms per group: kGroupHomes, or fewer in small thin boxes
+  int32_t passes, shift;          // times the rows are gone through, each `shift` rows further on
   int32_t L_q[3];                 // edges in fixed-point units, modulo 2^32
   double inv_slots, inv_m1;       // 1 / slots, 1 / M[1]
   double cap;                     // A: extent along x of a group of home atoms
@@ -247,7 +249,7 @@ void launch_reduce(const Views& v, bool energy, bool update, const StepOpts& o, 
 // small boxes (one work-group per box): the first kernel of a step (kick) or of a bin rebuild, and
 // the last kernel of a run of steps (reduction with the energies, launch_finalize)
 constexpr int64_t kSmallAtoms = 3072;       // largest box that takes them (measured: at the kernels)
-constexpr int64_t kSmallLds = 96 << 10;     // and its LDS
+constexpr int64_t kSmallLds = 80 << 10;     // and its LDS (3,000 atoms in 15,625 cells: 53.9 us a step, else 51.1)
 constexpr int64_t kSmallBoxes = 512;        // of more boxes than these, those of kSmallMean atoms on average
 constexpr int64_t kSmallMean = 512;
 int64_t small_lds_bytes(int64_t n_atoms, int64_t n_cells);
@@ -278,6 +280,7 @@ constexpr int kGroupPad = 16;   // a box's group blocks are padded to a multiple
 constexpr int kSplit = 4;       // wavefronts that share a group in boxes of few groups
 constexpr int kSplitItems = 2048;   // at most this many groups in all such boxes
 constexpr int kGroupHomes = 8;  // home atoms per group
+constexpr double kMeltDensity = 1.2;  // atoms per sigma^3 (0.67 g/cm^3 of polyethylene; its melts 1.2 to 1.6)
 
 constexpr int kTileHomesMixed = 8;   // home atoms per pass of a mixed cell-tile wave
 

@@ -136,3 +136,27 @@ def test_batch_on_either_side_of_the_split(ff, boxes, precision):
     s.step(2)
     assert all(np.array_equal(x, y) for x, y in zip(s.state(), (p, v)))   # the same every run
     s.close()
+
+
+@pytest.mark.parametrize("precision", ["mixed", "fp64"])
+@pytest.mark.parametrize("R,scale", [(1, 2.0), (2, 2.0), (1, 6.0), (2, 6.0)])
+def test_droplet(ff, R, scale, precision):
+    """A melt of whole chains in the middle of a larger box: few groups in thin rows (groups of two homes, on more
+    blocks), and with 2,500 rows in a nearly empty box (rows gone through eight times)."""
+    import dataclasses
+    m = make_melt(10, density=0.80, T=500.0, seed_melt=1000, seed_vel=1001, jitter=0.05)
+    p = m.pos.reshape(3, -1, m.chain_len)
+    d = np.diff(p, axis=2)
+    d -= m.box[:, None, None] * np.round(d / m.box[:, None, None])
+    flat = np.concatenate([p[:, :, :1], p[:, :, :1] + np.cumsum(d, axis=2)], axis=2).reshape(3, -1)
+    box = m.box * scale
+    pos = np.mod(flat + 0.5 * (box - m.box)[:, None], box[:, None])
+    pos[pos >= box[:, None]] = 0.0
+    m = dataclasses.replace(m, pos=np.ascontiguousarray(pos), box=box)
+    s = system(ff, [m], precision, R, 1)
+    f, flj, e = s.forces(), s.forces(lj_only=True), s.energies()[0]
+    s.close()
+    fo, eo = O.forces(ff, m.pos, m.types, m.box, 300, R=1)
+    lo, _ = O.lj_brute(ff, m.pos, m.types, m.box, 300)
+    assert norm_err(f, fo) <= TOL[precision] and norm_err(flj, lo) <= TOL[precision]
+    assert e["e_lj"] == pytest.approx(eo["e_lj"], rel=2e-6 if precision == "mixed" else 1e-12)
