@@ -252,7 +252,6 @@ GroupDev group_work(const md_forcefield* ff, const md_config* cfg, int64_t n, co
   g.passes = thin ? 3 : (fill < 0.02 ? 8 : 1);
   g.slots = row_groups(n, B, g.homes);
   g.items = (int32_t)(rows * g.slots);
-  g.shift = (int32_t)(rows / g.passes);
   g.blocks = (int32_t)((std::min<int64_t>(g.items, most) + kGroupPad - 1) / kGroupPad * kGroupPad);
   g.inv_slots = 1.0 / (double)g.slots;
   g.inv_m1 = 1.0 / (double)B.M[1];
@@ -261,11 +260,6 @@ GroupDev group_work(const md_forcefield* ff, const md_config* cfg, int64_t n, co
   // stay below 64 A (payload_ok: (R + 2) edge < 63 A, so the cap is at least edge - 1)
   g.cap = ff->rc;
   if (cfg->precision == MD_PREC_MIXED) g.cap = std::min(ff->rc, 62.0 - ff->rc - B.edge[0]);
-  // The gap covers the FP32 rounding of reaches and filter (and what the order along x leaves open, 1e-6 of a
-  // cell): in the mixed form, whose coordinates round to 2^-17 A at most, in A; in FP64, whose lengths
-  // may have any scale, as a part of the cutoff.
-  g.gap = cfg->precision == MD_PREC_MIXED ? 1e-3f : (float)(1e-4 * ff->rc);
-  g.rc_gap = (float)ff->rc + g.gap;
   return g;
 }
 

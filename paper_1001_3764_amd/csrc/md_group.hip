@@ -119,11 +119,12 @@ __device__ inline float lane_value_f(float x, int k) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), k));
 }
 
+// gap, rc: what is added to every reach (launch_e), the cutoff plus it.
 // NW wavefronts work on one group, each on every NW-th batch of its candidates (NW > 1: boxes with
 // too few groups to fill the chip); their sums are added in wave order.
 template <bool FP64, bool ENERGY, bool UNI, int NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(kGroupEu<FP64>)))
-void k_lj_group(Views v, FFDev ff, LjPair<float> cf, LjPair<double> cd) {
+void k_lj_group(Views v, FFDev ff, LjPair<float> cf, LjPair<double> cd, float gap, float rc) {
   using G = Geo<FP64>;
   using PayT = typename G::Pay;
   using Cand = typename G::Cand;
@@ -165,11 +166,11 @@ void k_lj_group(Views v, FFDev ff, LjPair<float> cf, LjPair<double> cd) {
   double e = 0.0, es = 0.0, w = 0.0;
 
   const int S = Q.slots, items = Q.items, stride = Q.blocks, KH = Q.homes;
-  const int passes = Q.passes;
+  const int passes = Q.passes, shift = passes > 1 ? M1 * M2 / passes : 0;
   for (int pass = 0; pass < passes; ++pass)
   for (int item = blk - B.lj_blk_off; item < items; item += stride) {
     const int row_of = uni((int)(((double)item + 0.5) * Q.inv_slots));          // item / S
-    int row = row_of + pass * Q.shift;
+    int row = row_of + pass * shift;
     row -= row >= M1 * M2 ? M1 * M2 : 0;
     const int kz = uni((int)(((double)row + 0.5) * Q.inv_m1)), ky = row - kz * M1;
     const int row0 = B.cell_off + row * M0;
@@ -330,7 +331,6 @@ void k_lj_group(Views v, FFDev ff, LjPair<float> cf, LjPair<double> cd) {
         };
         // ---- the candidates: one pass per periodic image along x that the group reaches ----
         int im = 0, im_left = -1;   // this pass's image; bit 0 / 1: image -1 / +1 still to do
-        const float gap = Q.gap, rc = Q.rc_gap;
         const float rcf = rc * rc * (G::kUnit * G::kUnit);
         do {
           // the runs, one stencil row per lane
@@ -497,8 +497,14 @@ template <bool FP64, bool ENERGY>
 void launch_e(const Views& v, const FFDev& ff, hipStream_t s) {
   const LjPair<float> cf = make_pair<float>(ff);
   const LjPair<double> cd = make_pair<double>(ff);
+  // The gap is added to every reach and to the filter for their FP32 rounding (and what the order along x leaves
+  // open, 1e-6 of a cell): in the mixed form, whose coordinates round to 2^-17 A at most, in A; in FP64, whose
+  // lengths may have any scale, as a part of the cutoff.
+  const double rc = std::sqrt(ff.rc2);
+  const float gap = FP64 ? (float)(1e-4 * rc) : 1e-3f, reach = (float)rc + gap;
   const dim3 g((v.n_lj_blocks + kXcds - 1) / kXcds * kXcds);
-#define MDK_GROUP(U, NW) hipLaunchKernelGGL((k_lj_group<FP64, ENERGY, U, NW>), g, dim3(64 * NW), 0, s, v, ff, cf, cd)
+#define MDK_GROUP(U, NW) \
+  hipLaunchKernelGGL((k_lj_group<FP64, ENERGY, U, NW>), g, dim3(64 * NW), 0, s, v, ff, cf, cd, gap, reach)
   if (v.lj_wave_mask & 1) {
     if (ff.uniform_lj) MDK_GROUP(true, 1);
     else MDK_GROUP(false, 1);

@@ -71,13 +71,12 @@ struct BoxDev {
 // Per box, for the group kernel (md_group.hip).
 struct GroupDev {
   int32_t slots, items, blocks;   // work items per row of cells and in all, per pass; blocks of this box
-  int32_t waves;                  // wavefronts per group: 1, or kSplit in small boxes
-  int32_t homes;                  // home atoms per group: kGroupHomes, or fewer in small thin boxes
-  int32_t passes, shift;          // times the rows are gone through, each `shift` rows further on
+  uint8_t waves;                  // wavefronts per group: 1, or kSplit in small boxes
+  uint8_t homes;                  // home atoms per group: kGroupHomes, or fewer in small thin boxes
+  uint16_t passes;                // times the rows are gone through, each 1 / passes of them further on
   int32_t L_q[3];                 // edges in fixed-point units, modulo 2^32
   double inv_slots, inv_m1;       // 1 / slots, 1 / M[1]
   double cap;                     // A: extent along x of a group of home atoms
-  float gap, rc_gap;              // added to every reach; the cutoff plus it
 };
 
 // Force-field constants in the form the kernels use (built on the host).
