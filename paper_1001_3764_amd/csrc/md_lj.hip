@@ -524,8 +524,9 @@ constexpr int kRunBatch = 2;      // windows whose loads are in flight together
 constexpr double kFilterGap = 1e-3;   // A added to the filter's reach: the rounding of its FP32 distances
 constexpr int kStage = 288;           // candidates held in LDS (16 B each): 24 waves per CU with the rest (at 304, 21)
 
+// (16 homes: 5 waves per SIMD with 12 registers spilled 179 us, 4 without 189, 300,000 atoms, R = 2)
 template <bool ENERGY, bool UNI, int KMAX, bool BRANCHLESS>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(KMAX >= 16 ? 4 : 6)))
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(KMAX >= 16 ? (ENERGY ? 4 : 5) : 6)))
 void k_lj_cell(Views v, FFDev ff, LjPair<float> cf, LjPair<double> cd) {
   constexpr int LV = KMAX == 16 ? 4 : (KMAX == 8 ? 3 : 2);   // log2(KMAX)
   static_assert((1 << LV) == KMAX, "KMAX must be 4, 8 or 16");
