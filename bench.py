@@ -70,19 +70,24 @@ def candidate_and_pair_counts(pos, box, start, M, R, rc, n_chains, chain_len):
 
 
 TRAFFIC_RECORD = os.path.join(ROOT, "profiles", "lj_cell_mixed_melt300k_traffic.json")
-LJ_SOURCE = os.path.join(ROOT, "paper_1001_3764_amd", "csrc", "md_lj.hip")
+CSRC = os.path.join(ROOT, "paper_1001_3764_amd", "csrc")
+LJ_SOURCES = [os.path.join(CSRC, f) for f in ("md_lj.hip", "md_group.hip", "md_lj_common.h", "md_internal.h")]
 
 
 def lj_source_hash():
-    """SHA-256 of the LJ kernels' source with comments and blank lines left out, so that the
-    counter record follows the code, not its commentary."""
+    """SHA-256 of the sources the LJ kernels are compiled from (the kernels, what they share and the
+    layout constants) with comments and blank lines left out, so that the counter record follows
+    the code, not its commentary."""
     import hashlib
     import re
-    with open(LJ_SOURCE) as fh:
-        text = fh.read()
-    lines = [re.sub(r"//.*$", "", line).rstrip() for line in text.splitlines()]
-    code = "\n".join(line for line in lines if line.strip())
-    return hashlib.sha256(code.encode()).hexdigest()
+    digest = hashlib.sha256()
+    for path in LJ_SOURCES:
+        with open(path) as fh:
+            text = fh.read()
+        lines = [re.sub(r"//.*$", "", line).rstrip() for line in text.splitlines()]
+        digest.update("\n".join(line for line in lines if line.strip()).encode())
+        digest.update(b"\n\0")
+    return digest.hexdigest()
 
 
 def counter_record(kernel_name):

@@ -56,3 +56,24 @@ def test_tuning_classes():
     t = bench.tuning_classes([6300, 9900, 120000], [(2, 2, 16), (2, 2, 8), (2, 2, 8)])
     assert t == {"R2/K2/H16": {"boxes": 1, "atoms_min": 6300, "atoms_max": 6300},
                  "R2/K2/H8": {"boxes": 2, "atoms_min": 9900, "atoms_max": 120000}}
+
+
+def test_source_hash_covers_what_the_kernels_share(monkeypatch, tmp_path):
+    """A change of code (not of a comment) in any of the sources the LJ kernels are built from changes the hash."""
+    import os
+    import shutil
+    names = ["md_lj.hip", "md_group.hip", "md_lj_common.h", "md_internal.h"]
+    csrc = os.path.join(bench.ROOT, "paper_1001_3764_amd", "csrc")
+    monkeypatch.setattr(bench, "LJ_SOURCES", [str(tmp_path / n) for n in names])
+    for n in names:
+        shutil.copy(os.path.join(csrc, n), tmp_path / n)
+    before = bench.lj_source_hash()
+    seen = {before}
+    for n in names:
+        text = (tmp_path / n).read_text()
+        (tmp_path / n).write_text("// a comment\n" + text)
+        assert bench.lj_source_hash() == before
+        (tmp_path / n).write_text(text + "\nconstexpr int kMore = 1;\n")
+        seen.add(bench.lj_source_hash())
+        (tmp_path / n).write_text(text)
+    assert len(seen) == 1 + len(names)
