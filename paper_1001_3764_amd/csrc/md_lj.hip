@@ -7,10 +7,11 @@
 // thread-per-atom kernel does), so each atom's force is a private sum: no atomics,
 // and the order of the sum is fixed by the sorted cell lists.
 //
-// Coordinates come from the sorted payload, relative to the centre of each atom's
-// cell.  A neighbour cell at offset (ox, oy, oz) contributes x_j + (ox, oy, oz) * edge
-// in the home cell's frame.  Mixed precision keeps these as int32 fixed point
-// (2^-25 A), so x_i - x_j is an exact integer rounded once to FP32; FP64 uses doubles.
+// Coordinates come from the sorted payload.  k_lj_cell's are box coordinates modulo 128 A.  The
+// lists' and the half shell's are relative to the centre of each atom's cell: a neighbour cell
+// at offset (ox, oy, oz) contributes x_j + (ox, oy, oz) * edge in the home cell's frame.  Mixed
+// precision keeps them as int32 fixed point (2^-25 A), so x_i - x_j is an exact integer rounded
+// once to FP32; FP64 uses doubles.
 //
 // Kernels (the rest of the cell path is in md_group.hip):
 //   k_lj_cell        mixed precision, one wavefront per home cell: the cell's atoms are
@@ -311,9 +312,9 @@ __device__ __forceinline__ void sum_homes(int ln, P (&ax)[KMAX], P (&ay)[KMAX], 
   sz = val[2];
 }
 
-// Occupancy targets (measured): the mixed form with 8 homes is held to 6 waves per SIMD (80
-// VGPRs; it uses 73, with no vector spills), 4 homes to 8 and 16 homes to 4; the FP64 form
-// (K = 4) fits 8.
+// Occupancy: the mixed form with 8 homes is held to 6 waves per SIMD (80 VGPRs; it uses 77 to 79, and with
+// energies spills 7 to 12 of them).  The bounds of the other forms are not met or not reached: 4 homes run
+// at 6 waves (77 to 79 VGPRs; with energies 4 or 5), 16 at 5 (with energies 4), FP64 at 5 or 6 (72 to 91).
 // (the homes and the sorted order are those of the last build, the payload the one refreshed since)
 template <bool FP64, bool ENERGY, bool UNI, int KMAX>
 __global__ __launch_bounds__(64 * kTileWaves)
@@ -509,12 +510,13 @@ void k_lj_tile(Views v, FFDev ff, LjPair<float> cf, LjPair<double> cd) {
 // goes, in the frame of the cell's first atom, to a list in LDS, which is then taken 64 at a time
 // against the homes, held wave-uniform.  The payload is in box coordinates (modulo 128 A).
 //
-// Bound: VALU issue (1,419 instructions per cell of 5.1 atoms at R = 2, about half of them pairs: 24 for
+// Bound: VALU instructions (1,419 per cell of 5.1 atoms at R = 2, about half of them pairs: 24 for
 // each home and 64 candidates; the rest set-up, 10 windows of 35 and the sums).  The form before listed
 // every candidate's index in LDS and gathered the payload twice (1,565 instructions).  LJ pass, event
 // timing: 300,000 atoms 159 -> 152 us; a step of 24 boxes of 453,600 atoms 272 -> 262 us, of 3,000 atoms
-// 40.0 -> 38.7 us, of 3,000,000 atoms 1,630 -> 1,618 us.  Force error against FP64 as before (rms 5.06e-7
-// over 24 melts).  Measured as well: the homes by scalar loads, no change.
+// 40.0 -> 38.7 us, of 3,000,000 atoms 1,630 -> 1,618 us.  LJ force error as before (12 relaxed
+// melts of 3,000 and 15,000 atoms against 80-bit arithmetic: rms 5.16e-7 and 5.17e-7 of the RMS force,
+// largest 6.8e-6 and 6.7e-6).  Measured as well: the homes by scalar loads, no change.
 // fixed-point coordinates modulo 2^32
 __device__ inline int fix_add(int a, int b) { return (int)((uint32_t)a + (uint32_t)b); }
 __device__ inline int fix_sub(int a, int b) { return (int)((uint32_t)a - (uint32_t)b); }

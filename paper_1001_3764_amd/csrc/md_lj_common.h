@@ -175,17 +175,9 @@ __device__ inline double lane_value(double x, int k) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
-// Minimum and maximum over lanes [0, K) (K = 1, 2, 4, 8 or 16; the other lanes of the first
-// 16-lane row hold the neutral element), as a vector-register value on every lane: a
-// butterfly over lane bits 0-3 within the row (xor 1, xor 2, the half-row mirror, xor 8), then
-// lane 0's result moved to every lane.
-template <typename T>
-__device__ inline T box_top();
-template <>
-__device__ inline int box_top<int>() { return 0x7fffffff; }
-template <>
-__device__ inline double box_top<double>() { return __builtin_huge_val(); }
-
+// Minimum and maximum over lanes [0, K) (K = 1, 2, 4, 8 or 16), as a vector-register value on every
+// lane: a butterfly over the log2(K) lowest lane bits (xor 1, xor 2, the half-row mirror, xor 8),
+// then lane 0's result moved to every lane.
 template <typename T>
 __device__ __forceinline__ T in_vgpr(T x) {
   if constexpr (sizeof(T) == 4) asm volatile("" : "+v"(x));

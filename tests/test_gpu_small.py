@@ -84,3 +84,29 @@ def test_many_boxes(ff, boxes, chains, precision, kernel):
     assert a.energies() == b.energies()
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("precision,kernel", [("mixed", 1), ("fp64", 2)])
+@pytest.mark.parametrize("edge", [123.0, 131.5])
+def test_sparse_grids(ff, edge, precision, kernel):
+    """Either side of the LDS line: 3,000 atoms in 23^3 cells (73 kB of LDS) and in 25^3 (the separate kernels)."""
+    from paper_1001_3764_amd.md import MDSystem
+    m = make_melt(250, chain_len=12, density=0.045, T=400.0, seed_melt=91, seed_vel=92, jitter=0.05)
+    p = m.pos.reshape(3, -1, m.chain_len)
+    d = np.diff(p, axis=2)
+    d -= m.box[:, None, None] * np.round(d / m.box[:, None, None])
+    p = np.concatenate([p[:, :, :1], p[:, :, :1] + np.cumsum(d, axis=2)], axis=2).reshape(3, -1)
+    box = np.full(3, edge)
+    assert (box > m.box).all()
+    args = (ff, [m.n_chains], box[None, :], [330.0], np.ascontiguousarray(np.mod(p, box[:, None])), m.vel, m.types)
+    kw = dict(chain_len=12, precision=precision, cell_div=2, lj_kernel=kernel)
+    print("N=%d edge %.1f %s" % (m.n_atoms, edge, kw), flush=True)
+    a, b = MDSystem(*args, use_graph=True, **kw), MDSystem(*args, use_graph=False, **kw)
+    for n in (3, 9):
+        a.step(n)
+        b.step_timed(n)
+        for x, y in zip(a.state() + a.bins(), b.state() + b.bins()):
+            assert np.array_equal(x, y)
+        assert a.energies() == b.energies()
+    a.close()
+    b.close()
