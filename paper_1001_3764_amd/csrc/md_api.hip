@@ -247,10 +247,11 @@ GroupDev group_work(const md_forcefield* ff, const md_config* cfg, int64_t n, co
   const bool thin = split && fill < 0.5 && (kGroupHomes - 1) * B.L[0] * (double)rows / (double)n > ff->rc;
   int64_t most = std::max<int64_t>(n / 4, 1);
   if (thin) most = std::max(most, std::min<int64_t>(n, kReduceChunk));
-  g.waves = split && !thin ? kSplit : 1;
-  g.homes = thin ? 2 : kGroupHomes;
-  g.passes = thin ? 3 : (fill < 0.02 ? 8 : 1);
-  g.slots = row_groups(n, B, g.homes);
+  const int waves = split && !thin ? kSplit : 1, homes = thin ? 2 : kGroupHomes;
+  const int passes = thin ? 3 : (fill < 0.02 ? 8 : 1);
+  g.form = waves | homes << 8 | passes << 16;
+  g.shift = (int32_t)(rows / passes);
+  g.slots = row_groups(n, B, homes);
   g.items = (int32_t)(rows * g.slots);
   g.blocks = (int32_t)((std::min<int64_t>(g.items, most) + kGroupPad - 1) / kGroupPad * kGroupPad);
   g.inv_slots = 1.0 / (double)g.slots;
@@ -394,7 +395,7 @@ size_t carve(const Plan& p, char* base, Views* v) {
   t.n_atom_blocks = p.n_atom_blocks;
   t.n_lj_blocks = p.n_lj_blocks;
   t.box_pay = p.prec == MD_PREC_MIXED && !p.group && !p.half && !p.nl_cap;
-  for (const GroupDev& g : p.groups) t.lj_wave_mask |= g.waves == kSplit ? 2 : 1;
+  for (const GroupDev& g : p.groups) t.lj_wave_mask |= g.waves() == kSplit ? 2 : 1;
   t.boxes = (const BoxDev*)take(sizeof(BoxDev) * p.n_boxes);
   t.blk_box = (const int32_t*)take(4 * (size_t)p.n_atom_blocks);
   t.lj_blk_box = (const int32_t*)take(4 * (size_t)(p.group ? p.n_lj_blocks / kGroupPad : p.n_lj_blocks));

@@ -158,7 +158,7 @@ void k_lj_group(Views v, FFDev ff, LjPair<float> cf, LjPair<double> cd, float ga
   const int box = v.lj_blk_box[blk / kGroupPad];
   const BoxDev& B = v.boxes[box];
   const GroupDev& Q = v.groups[box];
-  if (Q.waves != NW) return;   // a box of the other launch
+  if (Q.waves() != NW) return;   // a box of the other launch
   const PayT* __restrict__ pay = static_cast<const PayT*>(v.payload);
   const int32_t* __restrict__ cs = v.cell_start;
   const int R = v.R, W = 2 * R + 1;
@@ -167,17 +167,18 @@ void k_lj_group(Views v, FFDev ff, LjPair<float> cf, LjPair<double> cd, float ga
   const int oz = (int)(((float)ln + 0.5f) * rcp_f((float)W)) - R, oy = ln - (oz + R) * W - R;
   double e = 0.0, es = 0.0, w = 0.0;
 
-  const int S = Q.slots, items = Q.items, stride = Q.blocks, KH = Q.homes;
-  const int passes = Q.passes, shift = passes > 1 ? M1 * M2 / passes : 0;
-  for (int pass = 0; pass < passes; ++pass)
-  for (int item = blk - B.lj_blk_off; item < items; item += stride) {
+  const int S = Q.slots, items = Q.items, stride = Q.blocks, KH = Q.homes();
+  const int passes = Q.passes(), shift = Q.shift;
+  for (int item = blk - B.lj_blk_off, pass = 0; item < items;) {   // (each item's passes, then the next)
     const int row_of = uni((int)(((double)item + 0.5) * Q.inv_slots));          // item / S
     int row = row_of + pass * shift;
     row -= row >= M1 * M2 ? M1 * M2 : 0;
     const int kz = uni((int)(((double)row + 0.5) * Q.inv_m1)), ky = row - kz * M1;
     const int row0 = B.cell_off + row * M0;
     const int rs = uni(cs[row0]), re = uni(cs[row0 + M0]);
-    for (int p0 = rs + (pass * S + item - row_of * S) * KH; p0 < re; p0 += passes * S * KH) {
+    const int at = pass * S + item - row_of * S;
+    if (++pass >= passes) { pass = 0; item += stride; }
+    for (int p0 = rs + at * KH; p0 < re; p0 += passes * S * KH) {
       const int kc = min(KH, re - p0);
       // Homes further than Q.cap along x from the group's first one start a group of their own
       // (sparse rows): the frame stays within the fixed-point range and the runs stay short.

@@ -71,12 +71,16 @@ struct BoxDev {
 // Per box, for the group kernel (md_group.hip).
 struct GroupDev {
   int32_t slots, items, blocks;   // work items per row of cells and in all, per pass; blocks of this box
-  uint8_t waves;                  // wavefronts per group: 1, or kSplit in small boxes
-  uint8_t homes;                  // home atoms per group: kGroupHomes, or fewer in small thin boxes
-  uint16_t passes;                // times the rows are gone through, each 1 / passes of them further on
+  // waves | homes << 8 | passes << 16 (one word: read by a scalar load).  Wavefronts per group: 1, or kSplit in
+  // small boxes; home atoms per group: kGroupHomes, or fewer in small thin boxes; times the rows are gone
+  // through, each `shift` rows further on
+  int32_t form, shift;
   int32_t L_q[3];                 // edges in fixed-point units, modulo 2^32
   double inv_slots, inv_m1;       // 1 / slots, 1 / M[1]
   double cap;                     // A: extent along x of a group of home atoms
+  __host__ __device__ int waves() const { return form & 0xff; }
+  __host__ __device__ int homes() const { return form >> 8 & 0xff; }
+  __host__ __device__ int passes() const { return form >> 16; }
 };
 
 // Force-field constants in the form the kernels use (built on the host).
