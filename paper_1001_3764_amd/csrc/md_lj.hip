@@ -526,7 +526,9 @@ constexpr int kRunBatch = 2;      // windows whose loads are in flight together
 constexpr double kFilterGap = 1e-3;   // A added to the filter's reach: the rounding of its FP32 distances
 constexpr int kStage = 288;           // candidates held in LDS (16 B each): 24 waves per CU with the rest (at 304, 21)
 
-// (16 homes: 5 waves per SIMD with 12 registers spilled 179 us, 4 without 189, 300,000 atoms, R = 2)
+// Registers: 16 homes, 5 waves per SIMD with 12 spilled 179 us, 4 without 189 (LJ pass, 300,000 atoms, R = 2);
+// 8 homes at 6 waves against 5, an evaluation of 300,000 atoms: with energies (12 spilled) 234 against 238 us,
+// two types (4 spilled) 186 against 191, two types with energies (22 spilled) 349 against 339.
 template <bool ENERGY, bool UNI, int KMAX, bool BRANCHLESS>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(KMAX >= 16 ? (ENERGY ? 4 : 5) : 6)))
 void k_lj_cell(Views v, FFDev ff, LjPair<float> cf, LjPair<double> cd) {
