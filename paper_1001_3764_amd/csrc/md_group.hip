@@ -24,7 +24,7 @@
 // atoms, 48 against 43 us at 24,000; the groups of all such boxes together count: 24 boxes of 12,000 atoms
 // 347 against 195 us, 100 of 3,000 375 against 203).  Measured against the kernels it replaces (LJ pass, event
 // timing): one lane per atom, 3,000 atoms, FP64, R = 1: 388 -> 19 us; 36,720 atoms, mixed, R = 1:
-// 517 -> 45 us; the FP64 cell tile, 300,000 atoms, R = 2: 242 -> 205 us.
+// 517 -> 45 us; the FP64 cell tile, 300,000 atoms, R = 2: 246 -> 199 us.
 #include "md_lj_common.h"
 
 namespace mdk {
